@@ -66,7 +66,7 @@ def kernel_source_sha():
     csrc = os.path.join(ROOT, "paper_1402_4876_amd", "csrc")
     files = sorted(os.path.join(csrc, f) for f in os.listdir(csrc)
                    if f in ("dp_common.h", "dp_fill.h", "band.h", "plan.h", "dp_misc.hip") or
-                   f.startswith(("fill_", "persistent_", "side_")))
+                   f.startswith(("fill_", "persistent_", "side_", "seed")))
     return _sha_of(files + [os.path.join(ROOT, "paper_1402_4876_amd", "build.py")])
 
 

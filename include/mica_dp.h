@@ -80,7 +80,7 @@ enum {
   MICA_OUT_START = 1u << 0,   /* write read_start and ref_start (runs the traceback) */
   MICA_OUT_CIGAR = 1u << 1,   /* write cigar and n_cigar (implies MICA_OUT_START) */
   MICA_FORCE_INT32 = 1u << 8, /* compute every pair with 32-bit scores */
-  MICA_PLAIN_LAUNCH = 1u << 9, /* one launch per length bucket instead of the persistent one */
+  MICA_PLAIN_LAUNCH = 1u << 9, /* every pair's full table, one launch per length bucket */
   MICA_NO_GRAPH = 1u << 10     /* enqueue the kernels one by one instead of as one HIP graph */
 };
 
@@ -261,12 +261,12 @@ mica_status_t mica_ctx_load_plan(mica_ctx_t ctx, const char *path);
 /* Counters of the last batch enqueued on ctx (synchronises `stream`). */
 typedef struct {
   int64_t n_pairs;      /* pairs in the batch */
-  int64_t n_items;      /* work items taken by the fill kernels */
+  int64_t n_items;      /* work items of the full-table fill kernels */
   int64_t n_saturated;  /* pairs re-run with 32-bit scores */
   int64_t n_waves;      /* resident waves of the persistent launch */
   int64_t scratch_bytes;
-  int64_t n_fallback;   /* pairs traced back from a full fill of direction bits (band too wide) */
-  int64_t n_deferred;   /* pairs whose band (17-64 diagonals) was refilled by a later launch */
+  int64_t n_fallback;   /* traced pairs whose traceback band is over 64 diagonals wide (or outside 16 bits) */
+  int64_t n_deferred;   /* traced pairs whose traceback band is 17-64 diagonals wide */
 } mica_batch_stats_t;
 mica_status_t mica_ctx_last_stats(mica_ctx_t ctx, void *stream, mica_batch_stats_t *out);
 

@@ -46,7 +46,7 @@ def build(verbose: bool = True) -> str:
     t0 = time.time()
     with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES), int(os.environ.get("MAX_JOBS", os.cpu_count() or 4)))) as ex:
         # longest first: the persistent kernels and the traceback fills
-        order = sorted(SOURCES, key=lambda f: (not f.startswith("persistent"), not f.endswith("_1.hip")))
+        order = sorted(SOURCES, key=lambda f: (not f.startswith(("persistent", "seed")), not f.endswith("_1.hip")))
         objs = list(ex.map(_compile, order))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC"] + objs + ["-o", tmp]

@@ -113,6 +113,37 @@ __device__ __forceinline__ Band band_of(const Params* __restrict__ prm, int m, i
   return Band{lo, w, w > kBandMaxW || (NP == 2 && (hib + 16L * se + so > 32767 || 16L * se + so > 32767))};
 }
 
+// Pairs by the width of their traceback's band, of those that do not go
+// through the lists of the banded fills (which are counted by their length).
+struct BandCount {
+  int wide, mid;  // over kBandMaxW diagonals (or outside the packed refill), over kBandInlineW
+};
+template <class V, int MODE>
+__device__ __forceinline__ void band_count(const Params* __restrict__ prm, int m, int n, int h0, int score, int ie,
+                                           int je, BandCount* c) {
+  constexpr bool EXT = (MODE == 2);
+  if (ie < 1 || je < 1) return;
+  const int cls = prm->class_of_m[m];
+  const int d0 = EXT ? 0 : class_lanes(cls) * class_rows(cls) - m;
+  const Band bd = band_of<V::kPairs, EXT>(prm, m, n, d0, h0, score - d0, ie, je);
+  if (bd.wide) c->wide++;
+  else if (bd.w > kBandInlineW) c->mid++;
+}
+
+// the lanes' counts to the batch's
+__device__ __forceinline__ void band_count_flush(const Params* __restrict__ prm, const BandCount& c) {
+  int w = c.wide, d = c.mid;
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) {
+    w += __shfl_xor(w, s, 64);
+    d += __shfl_xor(d, s, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    if (w) atomicAdd(&prm->counters[kCtrPruneWide], (uint32_t)w);
+    if (d) atomicAdd(&prm->counters[kCtrPruneMid], (uint32_t)d);
+  }
+}
+
 // The pending list of a slot: after the direction-bit (or band record)
 // area and the CIGAR staging of 8 pairs.
 __device__ __forceinline__ MICA_GLOBAL uint32_t* pending_list(const Params* __restrict__ prm, uint8_t* slot) {
@@ -219,6 +250,485 @@ __device__ __forceinline__ void band_route(const Params* __restrict__ prm,
     pend_list[*pend + (int)rank] = pj;
   }
   *pend += __builtin_popcountll(bal);
+}
+
+// What a band fill that looks for the result cell keeps beside its bits, per
+// strip of a lane: the best value of the lane's diagonal and the first row
+// that reaches it (local, extension), and the value on row m (semi-global,
+// extension; also of cells past the window, which the reader leaves out).
+// Outside extensions the pairs of a wave end on its last row together: pair h
+// has top[h] dummy rows above its read (score -1, values shifted by -top[h],
+// as in the fill), and rows and diagonals below count from the wave's row 0.
+template <class T, int NS>
+struct BandFind {
+  T best[NS], row[NS], end[NS];
+  T lim[NS];  // the last row of the diagonal inside read and window
+  T m;        // read lengths, packed (extension)
+  int top[2];
+};
+
+// The band DP of a wave's groups of 16 lanes, rows 1 to rows_u, in ns_u strips.
+// TRACE keeps the sign bits of every cell; FIND also keeps what tells the
+// result cell.  Rows up to mr_u may touch column 0 or lie left of it; rows
+// from tail_u on may be past the end of a pair (FIND).
+template <class V, int MODE, int NS, bool TRACE, bool FIND>
+__device__ __forceinline__ void band_refill(const Params* __restrict__ prm, const int* dlo, const int* W,
+                                            const int* d0, const int* h0, const bool* act, int rows_u, int ns_u,
+                                            int mr_u, int tail_u, const uint32_t* gq, const uint16_t* gw,
+                                            MICA_GLOBAL uint32_t* rec, BandFind<typename V::T, NS>* find) {
+  typedef typename V::T T;
+  constexpr int NP = V::kPairs;
+  constexpr bool LOCAL = (MODE == 1);
+  constexpr bool EXT = (MODE == 2);
+  constexpr bool TRACK = (MODE != 0);
+  const int lane = threadIdx.x & 63;
+  const int l = lane & 15;
+  const int ns64 = ns_u * 64;
+  const int sa = prm->sa, sb = prm->sb, so = prm->so, se = prm->se;
+  const int oe = so + se;
+  const uint32_t tab_lo = ((uint32_t)sa & 0xFFFFu) | ((uint32_t)sb << 16);
+  const uint32_t tab_hi = ((uint32_t)sb & 0xFFFFu) | ((uint32_t)sb << 16);
+  const T negv = (T)V::kNeg;
+  const T ev = V::splat(se);
+  const T oev = V::splat(oe);
+  const T cg = V::splat(l * se);
+  const T og = V::splat(so + l * se);
+  const T e16 = V::splat(16 * se);
+  T floor_v = (T)0, floor1 = (T)0;
+  if constexpr (LOCAL) {
+    if constexpr (NP == 2) {
+      floor_v = V::make2(-d0[0], -d0[1]);
+      floor1 = V::make2(1 - d0[0], 1 - d0[1]);
+    } else {
+      floor_v = (T)(-d0[0]);
+      floor1 = (T)(1 - d0[0]);
+    }
+  }
+  // row 0: H(0, j) (nothing for j < 0); the insertion candidate of the row
+  // below is H - o - e there (I(0, j) is -inf); lanes past a pair's band
+  // hold -inf so they never feed it
+  T Hd[NS], Ic[NS], msk[NS];
+  uint32_t acc[NS];
+  const uint16_t* gwl = gw + l;
+  // the score table's low half as a register operand of the lookup
+  uint32_t tab_lo_v;
+  asm("v_mov_b32 %0, %1" : "=v"(tab_lo_v) : "s"(tab_lo));
+  constexpr uint32_t kFlip = 0x80008000u;  // signed <-> offset binary (16-bit halves)
+  auto pack = [&](int v0, int v1) -> T {
+    if constexpr (NP == 2) return V::make2(v0, v1);
+    else return (T)v0;
+  };
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    int hv[2] = {0, 0}, iv[2] = {0, 0};
+    bool mk[2] = {false, false}, neg[2] = {false, false};
+#pragma unroll
+    for (int h = 0; h < NP; ++h) {
+      const int gl = 16 * s + l;
+      const int j = dlo[h] + gl;
+      // (semi-global below dummy rows: they take 0 down to -top)
+      hv[h] = EXT ? (j == 0 ? h0[h] : h0[h] - (so + j * se)) : (FIND && !LOCAL ? 0 : -d0[h]);
+      iv[h] = hv[h] - oe;
+      neg[h] = j < 0;
+      if constexpr (FIND) neg[h] = neg[h] && find->top[h] == 0;
+      mk[h] = act[h] && gl < W[h];
+    }
+    uint32_t nm = 0;
+    if constexpr (NP == 2) {
+      Hd[s] = V::make2(hv[0], hv[1]);
+      Ic[s] = V::make2(iv[0], iv[1]);
+      msk[s] = (mk[0] ? 0xFFFFu : 0u) | (mk[1] ? 0xFFFF0000u : 0u);
+      nm = (neg[0] ? 0xFFFFu : 0u) | (neg[1] ? 0xFFFF0000u : 0u);
+    } else {
+      Hd[s] = (T)hv[0];
+      Ic[s] = (T)iv[0];
+      msk[s] = mk[0] ? ~0u : 0u;
+      nm = neg[0] ? ~0u : 0u;
+    }
+    Hd[s] = (T)bfi(nm, (uint32_t)negv, (uint32_t)Hd[s]);
+    Ic[s] = (T)bfi(msk[s] & ~nm, (uint32_t)Ic[s], (uint32_t)negv);
+    acc[s] = 0;
+  }
+
+  // a finding fill reads the codes one row ahead (its bands are often alone on
+  // their SIMD, so the LDS latency would show); one entry past the last row
+  // lies inside the wave's area
+  uint32_t q_next = 0, w_next[NS];
+  if constexpr (FIND) {
+    q_next = gq[0];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) w_next[s] = s < ns_u ? gwl[1 + 16 * s] : 0u;
+  }
+
+  auto row = [&](int i, auto par_c, auto masked_c) {
+    constexpr int PAR = decltype(par_c)::value;
+    constexpr bool MASKED = decltype(masked_c)::value;
+    // this row's number in every pair's part, and the pairs whose last row it is
+    T iv_row = (T)0;
+    uint32_t last = 0;
+    if constexpr (FIND) {
+      iv_row = NP == 2 ? (T)((uint32_t)i * 0x10001u) : (T)i;
+      if constexpr (MASKED && EXT) last = (uint32_t)V::negmask(V::sub((T)((uint32_t)iv_row ^ (uint32_t)find->m), V::splat(1)));
+    }
+    uint32_t qs;
+    if constexpr (FIND) {
+      qs = q_next;
+      q_next = gq[i];
+    } else {
+      qs = gq[i - 1];
+    }
+    T carry = negv;
+    T bnd = (T)0;
+    if constexpr (MASKED) {
+      // H(i, 0): the column-0 boundary
+      int bv[2] = {0, 0};
+#pragma unroll
+      for (int h = 0; h < NP; ++h) {
+        const int it = FIND ? i - find->top[h] : i;
+        bv[h] = LOCAL ? -d0[h] : (EXT ? h0[h] : -d0[h]) - (so + it * se);
+      }
+      bnd = pack(bv[0], bv[1]);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (s >= ns_u) break;
+      // window selector of column i + delta_lo + 16 s + l (each half its own pair)
+      uint32_t rsel;
+      {
+        uint32_t w;
+        if constexpr (FIND) {
+          w = w_next[s];
+          w_next[s] = gwl[i + 1 + 16 * s];
+        } else {
+          w = gwl[i + 16 * s];
+        }
+        if constexpr (NP == 2) rsel = __builtin_amdgcn_perm(w, w, 0x01010000u);
+        else rsel = w * 0x01010202u;
+      }
+      const T sc = (T)__builtin_amdgcn_perm(tab_hi, tab_lo_v, qs ^ rsel);
+      const T x = V::add(Hd[s], sc);
+      // insertion from the next diagonal one row up
+      T old = negv;
+      if (s + 1 < NS && s + 1 < ns_u) old = MICA_DPP(negv, Ic[s + 1 < NS ? s + 1 : s], kDppRor15);
+      const T Iv = MICA_DPP(old, Ic[s], kDppShl1);
+      T Hp = V::vmax(x, Iv);
+      if constexpr (LOCAL) Hp = V::vmax(Hp, floor_v);
+      if constexpr (MASKED) {
+        // cells left of column 0 do not exist; column 0 is the boundary
+        uint32_t zm = 0, nm = 0;
+#pragma unroll
+        for (int h = 0; h < NP; ++h) {
+          const int j = i + dlo[h] + 16 * s + l;
+          uint32_t half = NP == 2 ? (0xFFFFu << (16 * h)) : ~0u;
+          if constexpr (FIND) half = i > find->top[h] ? half : 0u;  // (the dummy rows have no column 0)
+          zm |= j == 0 ? half : 0u;
+          nm |= j < 0 ? half : 0u;
+        }
+        Hp = (T)bfi(zm, (uint32_t)bnd, (uint32_t)Hp);
+        Hp = (T)bfi(nm, (uint32_t)negv, (uint32_t)Hp);
+      }
+      // deletion: exclusive max-plus prefix over the row (strip-relative
+      // offsets; `carry` brings the strips to the left)
+      T Dv;
+      if constexpr (NP == 2) {
+        // in offset binary (sign bit flipped) -inf is 0, which the DPP
+        // moves write into lanes without a source: no copies of -inf
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        auto umax = [](uint32_t a, uint32_t b) -> uint32_t {
+          return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
+                                                                        __builtin_bit_cast(u16x2, b)));
+        };
+        uint32_t g = (uint32_t)V::add(Hp, cg) ^ kFlip;
+        g = umax(g, dpp_zero<kDppShr1>(g));
+        g = umax(g, dpp_zero<kDppShr2>(g));
+        g = umax(g, dpp_zero<kDppShr4>(g));
+        g = umax(g, dpp_zero<kDppShr8>(g));
+        if (s > 0) g = umax(g, (uint32_t)carry);
+        uint32_t excl = dpp_zero<kDppShr1>(g);
+        if (s > 0) excl = umax(excl, (uint32_t)carry);
+        Dv = V::sub((T)(excl ^ kFlip), og);
+        if (s + 1 < NS && s + 1 < ns_u) carry = (T)((uint32_t)V::sub((T)(dpp_zero<kDppBcast15>(g) ^ kFlip), e16) ^ kFlip);
+      } else {
+        T g = V::add(Hp, cg);
+        g = V::vmax(g, MICA_DPP(negv, g, kDppShr1));
+        g = V::vmax(g, MICA_DPP(negv, g, kDppShr2));
+        g = V::vmax(g, MICA_DPP(negv, g, kDppShr4));
+        g = V::vmax(g, MICA_DPP(negv, g, kDppShr8));
+        if (s > 0) g = V::vmax(g, carry);
+        const T excl = MICA_DPP(carry, g, kDppShr1);
+        Dv = V::sub(excl, og);
+        if (s + 1 < NS && s + 1 < ns_u) carry = V::sub(MICA_DPP(negv, g, kDppBcast15), e16);
+      }
+      const T Hv = V::vmax(Hp, Dv);
+      const T Tv = V::sub(Hv, oev);
+      const T Icn = V::vmax(V::sub(Iv, ev), Tv);
+      if constexpr (FIND && TRACK) {
+        // the diagonal's best and the first row that reaches it
+        uint32_t up = (uint32_t)V::negmask(V::sub(find->best[s], Hv));
+        if constexpr (MASKED) {
+          up &= ~(uint32_t)V::negmask(V::sub(find->lim[s], iv_row));
+          find->best[s] = (T)bfi(up, (uint32_t)Hv, (uint32_t)find->best[s]);
+        } else {
+          find->best[s] = V::vmax(find->best[s], Hv);
+        }
+        find->row[s] = (T)bfi(up, (uint32_t)iv_row, (uint32_t)find->row[s]);
+      }
+      if constexpr (FIND && MASKED && EXT) find->end[s] = (T)bfi(last, (uint32_t)Hv, (uint32_t)find->end[s]);
+      // sign bits: diagonal loses, deletion loses | deletion of the right
+      // cell extends, insertion of the cell below extends | H is zero
+      if constexpr (TRACE) {
+        const uint32_t p01 = __builtin_amdgcn_perm((uint32_t)V::sub(Dv, Hv), (uint32_t)V::sub(x, Hv), V::kSignSel);
+        const uint32_t p23 = __builtin_amdgcn_perm((uint32_t)V::sub(Tv, Icn), (uint32_t)V::sub(Tv, V::sub(Dv, ev)),
+                                                   V::kSignSel);
+        constexpr uint32_t M0 = 0x01010101u << (4 * PAR), M1 = 0x02020202u << (4 * PAR),
+                           M2 = 0x04040404u << (4 * PAR);
+        uint32_t a = acc[s];
+        a = and_or(p01, M0, a);
+        a = and_or(p23, M1, a);
+        if constexpr (LOCAL) {
+          const uint32_t zr = (uint32_t)V::sub(Hv, floor1);
+          a = and_or(__builtin_amdgcn_perm(zr, zr, V::kSignSel), M2, a);
+        }
+        acc[s] = a;
+      }
+      Hd[s] = Hv;
+      Ic[s] = (T)bfi(msk[s], (uint32_t)Icn, (uint32_t)negv);
+    }
+  };
+  auto flush = [&](int i) {  // rows i and i + 1 (1-based i odd)
+    if constexpr (!TRACE) return;
+    const size_t base = (size_t)((i - 1) >> 1) * (size_t)ns64 + (size_t)lane;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (s >= ns_u) break;
+      rec[base + (size_t)(s * 64)] = acc[s];
+      acc[s] = 0;
+    }
+  };
+  int i = 1;
+  auto careful = [&](int upto) {  // rows before `upto`, in steps of two
+    for (; i <= rows_u && i < upto; i += 2) {
+      row(i, std::integral_constant<int, 0>{}, std::true_type{});
+      if (i + 1 <= rows_u) row(i + 1, std::integral_constant<int, 1>{}, std::true_type{});
+      flush(i);
+    }
+  };
+  auto plain = [&](int upto) {
+    for (; i + 1 < upto; i += 2) {
+      row(i, std::integral_constant<int, 0>{}, std::false_type{});
+      row(i + 1, std::integral_constant<int, 1>{}, std::false_type{});
+      flush(i);
+    }
+  };
+  if constexpr (FIND) {
+    // (one copy of each loop: the rows below column 0, the plain rows, the
+    // rows from the first end of a pair on)
+    for (int part = 0; part < 2; ++part) {
+      careful(part == 0 ? mr_u + 1 : rows_u + 1);
+      if (part == 0) plain(tail_u <= rows_u ? tail_u : rows_u + 1);
+    }
+    if constexpr (!LOCAL && !EXT) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) find->end[s] = Hd[s];
+    }
+  } else {
+    careful(mr_u + 1);
+    plain(rows_u + 1);
+    if (i <= rows_u) {
+      row(i, std::integral_constant<int, 0>{}, std::false_type{});
+      flush(i);
+    }
+  }
+}
+
+// The walk from the result cell (ie, je) of pair p back through the band's
+// records (of rows top + 1 on), and the outputs it gives.  X = 16 / NP lanes
+// of a band group walk pair h together; every lane of the X holds the walk
+// state.  The band is W diagonals from dlo up.  Runs are staged in LDS (lst,
+// kWalkStage words), the ones past that in stg.
+//
+// What bounds it is the latency of its dependent loads, so each turn of the
+// loop has as few as it can: a lane takes C consecutive cells of the
+// diagonal (two rows share a record word), all its loads in flight at once,
+// which covers X * C cells; groups that turn into a gap there follow it in
+// the same turn, X cells at a time.  Every lane runs the same code whatever
+// its group's state, so the loads of all groups overlap: with a branch per
+// state the eight groups of an item took up to 100 us to walk in turn, and
+// 10 us each alone.
+constexpr int kWalkStage = 16;
+template <class V, int MODE>
+__device__ __forceinline__ void band_walk(const Params* __restrict__ prm, const MICA_GLOBAL uint32_t* rec,
+                                          uint32_t* lst, MICA_GLOBAL uint32_t* stg, int ns64, int p, int m, int n,
+                                          int ie, int je, int dlo, int W, int top = 0) {
+  constexpr bool LOCAL = (MODE == 1);
+  constexpr bool EXT = (MODE == 2);
+  constexpr int X = 16 / V::kPairs;
+  constexpr int C = 16;
+  const int lane = threadIdx.x & 63;
+  const int bg = lane >> 4;
+  const int h = (lane & 15) / X;
+  const int x = (lane & 15) - h * X;
+  const int lane0 = lane - x;
+  constexpr uint64_t xmask = (1ull << X) - 1;
+  const MICA_GLOBAL uint32_t* const mine = rec + bg * 16;
+  auto in_band = [&](int i, int j) -> bool {
+    const int gl = j - i - dlo;
+    return i >= 1 && gl >= 0 && gl < W;
+  };
+  // the record word of row pair rp (0-based rows 2 rp, 2 rp + 1) on a diagonal
+  auto word = [&](int rp, int gl) -> uint32_t {
+    return mine[(size_t)rp * (size_t)ns64 + (size_t)((gl >> 4) * 64 + (gl & 15))];
+  };
+  int i = ie, j = je;
+  int state = 0;  // 0: H, 1: D, 2: I
+  int nruns = 0, cur_op = -1, cur_len = 0;
+  bool bad = ie < 0 || ie > m || je < 0 || je > n;
+  bool done = bad;
+  auto close = [&]() {
+    if (cur_len > 0) {
+      if (x == 0) {
+        const uint32_t v = ((uint32_t)cur_len << 4) | (uint32_t)cur_op;
+        if (nruns < kWalkStage) lst[nruns] = v;
+        else stg[nruns] = v;
+      }
+      ++nruns;
+    }
+  };
+  auto emit = [&](int op, int len) {
+    if (op != cur_op) {
+      close();
+      cur_op = op;
+      cur_len = 0;
+    }
+    cur_len += len;
+  };
+  while (__ballot(!done) != 0) {
+    // ---- along the diagonal, from (i, j) up -------------------------------------
+    if (!done && state == 0) {
+      if (i == 0) {
+        if (EXT && j > 0) {  // an extension starts at the anchor: a leading deletion
+          emit(2, j);
+          j = 0;
+        }
+        done = true;
+      } else if (j == 0) {
+        if (!LOCAL) {
+          emit(1, i);  // a leading insertion (semi-global, extension)
+          i = 0;
+        }
+        done = true;
+      } else if (i > m || j > n || !in_band(i, j)) {
+        bad = done = true;
+      }
+    }
+    const bool diag = !done && state == 0;
+    // lane x: cells (i - c, j - c), x C <= c < (x + 1) C, the inside ones
+    int len = 0, next = 0;  // cells that go on along the diagonal; the state after the last
+    bool zero = false;
+    if (diag) {
+      const int i1 = i - x * C, j1 = j - x * C;
+      int inside = i1 < j1 ? i1 : j1;
+      inside = inside < 0 ? 0 : (inside > C ? C : inside);
+      const int r = i1 + top - 1;  // 0-based row of this lane's first cell
+      const int rp = r >> 1;
+      const int gl = j - i - dlo;
+      uint32_t wd[C / 2 + 1];
+#pragma unroll
+      for (int d = 0; d <= C / 2; ++d) wd[d] = word(rp - d > 0 ? rp - d : 0, gl);
+      // bit k: cell k (rows go down; a word's odd row comes first, and an even
+      // first row leaves the odd one of its word out)
+      uint32_t lose = 0, dl = 0, zr = 0;
+#pragma unroll
+      for (int d = 0; d <= C / 2; ++d) {
+        const uint32_t t = wd[d] >> (8 * h);
+        lose |= (((t >> 4) & 1u) | ((t & 1u) << 1)) << (2 * d);
+        dl |= (((t >> 20) & 1u) | (((t >> 16) & 1u) << 1)) << (2 * d);
+        if (LOCAL) zr |= (((t >> 6) & 1u) | (((t >> 2) & 1u) << 1)) << (2 * d);
+      }
+      const uint32_t odd = (uint32_t)(r & 1) ^ 1u;
+      lose >>= odd;
+      dl >>= odd;
+      zr >>= odd;
+      const uint32_t end = 1u << inside;
+      len = __builtin_ctz(lose | zr | end);
+      zero = LOCAL && len < inside && ((zr >> len) & 1u);
+      if (len < inside && !zero) next = ((dl >> len) & 1u) ? 2 : 1;
+    }
+    {
+      // the first lane of the group that stops before its last cell
+      const uint64_t full = (__ballot(diag && len == C) >> lane0) & xmask;
+      const uint64_t part = ~full & xmask;
+      const int f = part ? (int)__builtin_ctzll(part) : X - 1;
+      const int got = __shfl(len | (next << 8) | (zero ? 1 << 10 : 0), lane0 + f, 64);
+      if (diag) {
+        const int L = f * C + (got & 0xFF);
+        if (L > 0) {
+          emit(0, L);
+          i -= L;
+          j -= L;
+        }
+        state = (got >> 8) & 3;
+        if (got >> 10) done = true;  // H = 0: the local alignment starts here
+      }
+    }
+    // ---- along a gap, X cells ------------------------------------------------------
+    if (!done && state != 0 && (i < 1 || j < 1 || i > m || j > n)) bad = done = true;
+    const bool gap = !done && state != 0;
+    if (__ballot(gap) != 0) {
+      // a deletion at (i, j - x) extends when the bit its left neighbour keeps
+      // says so, an insertion at (i - x, j) by the cell above; in column or
+      // row 1 a gap can only open
+      const bool del = state == 1;
+      const int gi = del ? i : i - x - 1, gj = del ? j - x - 1 : j;
+      const bool look = gap && gi >= 1 && gj >= 1 && in_band(gi, gj);
+      bool ext = false;
+      if (look) {
+        const int r = gi + top - 1;
+        const uint32_t t = word(r >> 1, gj - gi - dlo) >> (8 * h + 4 * (r & 1));
+        ext = (del ? t >> 1 : t >> 17) & 1u;
+      }
+      const uint64_t cont = (__ballot(ext) >> lane0) & xmask;
+      const uint64_t part = ~cont & xmask;
+      if (gap) {
+        const int ones = part ? (int)__builtin_ctzll(part) : X;
+        const int L = part ? ones + 1 : X;  // cells 0..ones-1 extend, cell `ones` opens
+        emit(del ? 2 : 1, L);
+        if (del) j -= L;
+        else i -= L;
+        if (part) state = 0;
+        // (a run that would leave the matrix can only come from inconsistent
+        // bits: i or j is negative then, and the next turn flags it)
+        if (i < 0 || j < 0) bad = done = true;
+      }
+    }
+  }
+  close();
+  uint32_t st = 0;
+  if (bad) {
+    st |= kStInternal;
+    i = j = 0;
+    nruns = 0;
+  }
+  lds_wait();
+  if (prm->flags & kOutCigar) {
+    const int cap = prm->cigar_cap;
+    MICA_GLOBAL uint32_t* out = G(prm->cigar) + (size_t)p * (size_t)cap;
+    const int ncopy = nruns < cap ? nruns : cap;
+    // (lane 0 wrote the runs past the stage, and reads them back itself)
+    for (int y = x; y < ncopy; y += X)
+      if (nruns - 1 - y < kWalkStage) out[y] = lst[nruns - 1 - y];
+    if (x == 0)
+      for (int y = 0; y < ncopy && nruns - 1 - y >= kWalkStage; ++y) out[y] = stg[nruns - 1 - y];
+    if (nruns > cap) st |= kStCigarTrunc;
+    if (x == 0) G(prm->n_cigar)[p] = nruns > cap ? -nruns : nruns;
+  }
+  if (x == 0) {
+    if (prm->flags & (kOutStart | kOutCigar)) {
+      G(prm->read_start)[p] = i;
+      G(prm->ref_start)[p] = j;
+    }
+    G(prm->status)[p] = st;
+  }
 }
 
 // The banded traceback and the outputs of one work item (all lanes of the
@@ -336,190 +846,8 @@ __device__ __forceinline__ void band_traceback(const Params* __restrict__ prm,
   MICA_GLOBAL uint32_t* rec = (MICA_GLOBAL uint32_t*)slot;
   const int ns64 = ns_u * 64;
   if (rows_u > 0) {
-    const uint32_t tab_lo = ((uint32_t)sa & 0xFFFFu) | ((uint32_t)sb << 16);
-    const uint32_t tab_hi = ((uint32_t)sb & 0xFFFFu) | ((uint32_t)sb << 16);
-    const T negv = (T)V::kNeg;
-    const T ev = V::splat(se);
-    const T oev = V::splat(oe);
-    const T cg = V::splat(l * se);
-    const T og = V::splat(so + l * se);
-    const T e16 = V::splat(16 * se);
-    T floor_v = (T)0, floor1 = (T)0;
-    if constexpr (LOCAL) {
-      if constexpr (NP == 2) {
-        floor_v = V::make2(-d0[0], -d0[1]);
-        floor1 = V::make2(1 - d0[0], 1 - d0[1]);
-      } else {
-        floor_v = (T)(-d0[0]);
-        floor1 = (T)(1 - d0[0]);
-      }
-    }
-    // row 0: H(0, j) (nothing for j < 0); the insertion candidate of the row
-    // below is H - o - e there (I(0, j) is -inf); lanes past a pair's band
-    // hold -inf so they never feed it
-    T Hd[NS], Ic[NS], msk[NS];
-    uint32_t acc[NS];
-    const uint16_t* gwl = gw + l;
-    // the score table's low half as a register operand of the lookup
-    uint32_t tab_lo_v;
-    asm("v_mov_b32 %0, %1" : "=v"(tab_lo_v) : "s"(tab_lo));
-    constexpr uint32_t kFlip = 0x80008000u;  // signed <-> offset binary (16-bit halves)
-    auto pack = [&](int v0, int v1) -> T {
-      if constexpr (NP == 2) return V::make2(v0, v1);
-      else return (T)v0;
-    };
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      int hv[2] = {0, 0}, iv[2] = {0, 0};
-      bool mk[2] = {false, false}, neg[2] = {false, false};
-#pragma unroll
-      for (int h = 0; h < NP; ++h) {
-        const int gl = 16 * s + l;
-        const int j = dlo[h] + gl;
-        hv[h] = EXT ? (j == 0 ? h0[h] : h0[h] - (so + j * se)) : -d0[h];
-        iv[h] = hv[h] - oe;
-        neg[h] = j < 0;
-        mk[h] = act[h] && gl < W[h];
-      }
-      uint32_t nm = 0;
-      if constexpr (NP == 2) {
-        Hd[s] = V::make2(hv[0], hv[1]);
-        Ic[s] = V::make2(iv[0], iv[1]);
-        msk[s] = (mk[0] ? 0xFFFFu : 0u) | (mk[1] ? 0xFFFF0000u : 0u);
-        nm = (neg[0] ? 0xFFFFu : 0u) | (neg[1] ? 0xFFFF0000u : 0u);
-      } else {
-        Hd[s] = (T)hv[0];
-        Ic[s] = (T)iv[0];
-        msk[s] = mk[0] ? ~0u : 0u;
-        nm = neg[0] ? ~0u : 0u;
-      }
-      Hd[s] = (T)bfi(nm, (uint32_t)negv, (uint32_t)Hd[s]);
-      Ic[s] = (T)bfi(msk[s] & ~nm, (uint32_t)Ic[s], (uint32_t)negv);
-      acc[s] = 0;
-    }
-
-    auto row = [&](int i, auto par_c, auto masked_c) {
-      constexpr int PAR = decltype(par_c)::value;
-      constexpr bool MASKED = decltype(masked_c)::value;
-      const uint32_t qs = gq[i - 1];
-      T carry = negv;
-      T bnd = (T)0;
-      if constexpr (MASKED) {
-        // H(i, 0): the column-0 boundary
-        int bv[2] = {0, 0};
-#pragma unroll
-        for (int h = 0; h < NP; ++h) bv[h] = LOCAL ? -d0[h] : (EXT ? h0[h] : -d0[h]) - (so + i * se);
-        bnd = pack(bv[0], bv[1]);
-      }
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if (s >= ns_u) break;
-        // window selector of column i + delta_lo + 16 s + l (each half its own pair)
-        uint32_t rsel;
-        {
-          const uint32_t w = gwl[i + 16 * s];
-          if constexpr (NP == 2) rsel = __builtin_amdgcn_perm(w, w, 0x01010000u);
-          else rsel = w * 0x01010202u;
-        }
-        const T sc = (T)__builtin_amdgcn_perm(tab_hi, tab_lo_v, qs ^ rsel);
-        const T x = V::add(Hd[s], sc);
-        // insertion from the next diagonal one row up
-        T old = negv;
-        if (s + 1 < NS && s + 1 < ns_u) old = MICA_DPP(negv, Ic[s + 1 < NS ? s + 1 : s], kDppRor15);
-        const T Iv = MICA_DPP(old, Ic[s], kDppShl1);
-        T Hp = V::vmax(x, Iv);
-        if constexpr (LOCAL) Hp = V::vmax(Hp, floor_v);
-        if constexpr (MASKED) {
-          // cells left of column 0 do not exist; column 0 is the boundary
-          uint32_t zm = 0, nm = 0;
-#pragma unroll
-          for (int h = 0; h < NP; ++h) {
-            const int j = i + dlo[h] + 16 * s + l;
-            const uint32_t half = NP == 2 ? (0xFFFFu << (16 * h)) : ~0u;
-            zm |= j == 0 ? half : 0u;
-            nm |= j < 0 ? half : 0u;
-          }
-          Hp = (T)bfi(zm, (uint32_t)bnd, (uint32_t)Hp);
-          Hp = (T)bfi(nm, (uint32_t)negv, (uint32_t)Hp);
-        }
-        // deletion: exclusive max-plus prefix over the row (strip-relative
-        // offsets; `carry` brings the strips to the left)
-        T Dv;
-        if constexpr (NP == 2) {
-          // in offset binary (sign bit flipped) -inf is 0, which the DPP
-          // moves write into lanes without a source: no copies of -inf
-          typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-          auto umax = [](uint32_t a, uint32_t b) -> uint32_t {
-            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
-                                                                          __builtin_bit_cast(u16x2, b)));
-          };
-          uint32_t g = (uint32_t)V::add(Hp, cg) ^ kFlip;
-          g = umax(g, dpp_zero<kDppShr1>(g));
-          g = umax(g, dpp_zero<kDppShr2>(g));
-          g = umax(g, dpp_zero<kDppShr4>(g));
-          g = umax(g, dpp_zero<kDppShr8>(g));
-          if (s > 0) g = umax(g, (uint32_t)carry);
-          uint32_t excl = dpp_zero<kDppShr1>(g);
-          if (s > 0) excl = umax(excl, (uint32_t)carry);
-          Dv = V::sub((T)(excl ^ kFlip), og);
-          if (s + 1 < NS && s + 1 < ns_u) carry = (T)((uint32_t)V::sub((T)(dpp_zero<kDppBcast15>(g) ^ kFlip), e16) ^ kFlip);
-        } else {
-          T g = V::add(Hp, cg);
-          g = V::vmax(g, MICA_DPP(negv, g, kDppShr1));
-          g = V::vmax(g, MICA_DPP(negv, g, kDppShr2));
-          g = V::vmax(g, MICA_DPP(negv, g, kDppShr4));
-          g = V::vmax(g, MICA_DPP(negv, g, kDppShr8));
-          if (s > 0) g = V::vmax(g, carry);
-          const T excl = MICA_DPP(carry, g, kDppShr1);
-          Dv = V::sub(excl, og);
-          if (s + 1 < NS && s + 1 < ns_u) carry = V::sub(MICA_DPP(negv, g, kDppBcast15), e16);
-        }
-        const T Hv = V::vmax(Hp, Dv);
-        const T Tv = V::sub(Hv, oev);
-        const T Icn = V::vmax(V::sub(Iv, ev), Tv);
-        // sign bits: diagonal loses, deletion loses | deletion of the right
-        // cell extends, insertion of the cell below extends | H is zero
-        const uint32_t p01 = __builtin_amdgcn_perm((uint32_t)V::sub(Dv, Hv), (uint32_t)V::sub(x, Hv), V::kSignSel);
-        const uint32_t p23 = __builtin_amdgcn_perm((uint32_t)V::sub(Tv, Icn), (uint32_t)V::sub(Tv, V::sub(Dv, ev)),
-                                                   V::kSignSel);
-        constexpr uint32_t M0 = 0x01010101u << (4 * PAR), M1 = 0x02020202u << (4 * PAR),
-                           M2 = 0x04040404u << (4 * PAR);
-        uint32_t a = acc[s];
-        a = and_or(p01, M0, a);
-        a = and_or(p23, M1, a);
-        if constexpr (LOCAL) {
-          const uint32_t zr = (uint32_t)V::sub(Hv, floor1);
-          a = and_or(__builtin_amdgcn_perm(zr, zr, V::kSignSel), M2, a);
-        }
-        acc[s] = a;
-        Hd[s] = Hv;
-        Ic[s] = (T)bfi(msk[s], (uint32_t)Icn, (uint32_t)negv);
-      }
-    };
-    auto flush = [&](int i) {  // rows i and i + 1 (1-based i odd)
-      const size_t base = (size_t)((i - 1) >> 1) * (size_t)ns64 + (size_t)lane;
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        if (s >= ns_u) break;
-        rec[base + (size_t)(s * 64)] = acc[s];
-        acc[s] = 0;
-      }
-    };
-    int i = 1;
-    for (; i <= rows_u && i <= mr_u; i += 2) {
-      row(i, std::integral_constant<int, 0>{}, std::true_type{});
-      if (i + 1 <= rows_u) row(i + 1, std::integral_constant<int, 1>{}, std::true_type{});
-      flush(i);
-    }
-    for (; i + 1 <= rows_u; i += 2) {
-      row(i, std::integral_constant<int, 0>{}, std::false_type{});
-      row(i + 1, std::integral_constant<int, 1>{}, std::false_type{});
-      flush(i);
-    }
-    if (i <= rows_u) {
-      row(i, std::integral_constant<int, 0>{}, std::false_type{});
-      flush(i);
-    }
+    BandFind<T, NS> none;
+    band_refill<V, MODE, NS, true, false>(prm, dlo, W, d0, h0, act, rows_u, ns_u, mr_u, rows_u + 1, gq, gw, rec, &none);
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   lds_wait();
@@ -574,182 +902,9 @@ __device__ __forceinline__ void band_traceback(const Params* __restrict__ prm,
         G(prm->read_end)[p_] = ie_;
         G(prm->ref_end)[p_] = je_;
       }
-      uint32_t st = 0;
       MICA_GLOBAL uint32_t* stg =
           (MICA_GLOBAL uint32_t*)(slot + prm->dir_bytes) + (size_t)q * (size_t)prm->stage_stride;
-      int i = ie_, j = je_;
-      int state = 0;  // 0: H, 1: D, 2: I
-      int nruns = 0, cur_op = -1, cur_len = 0;
-      bool bad = ie_ < 0 || ie_ > m_ || je_ < 0 || je_ > n_;
-      const int lane0 = lane - x;
-      constexpr uint64_t xmask = (1ull << X) - 1;
-      auto sub = [&](bool pr) -> uint64_t { return (__ballot(pr) >> lane0) & xmask; };
-      auto first_clear = [&](uint64_t msk) -> int {
-        const uint64_t z = ~msk & xmask;
-        return z ? (int)__builtin_ctzll(z) : X;
-      };
-      constexpr int C = 64 / X;
-      constexpr int XC = X * C;
-      auto first_clear_xc = [&](uint64_t msk) -> int {
-        const uint64_t z = ~msk;
-        return z ? (int)__builtin_ctzll(z) : XC;
-      };
-      // the record word of cell (ii, jj) (1 <= ii, inside the band) and the
-      // bit offset of its row and pair half; kinds: +0 diagonal loses
-      // (second half-word: deletion loses), +1 deletion of the right cell
-      // extends (second: insertion of the cell below extends), +2 zero
-      auto in_band = [&](int ii, int jj) -> bool {
-        const int gl = jj - ii - dlo_;
-        return ii >= 1 && gl >= 0 && gl < W_;
-      };
-      auto word = [&](int ii, int jj, int* bit) -> uint32_t {
-        const int gl = jj - ii - dlo_;
-        *bit = 8 * h + 4 * ((ii - 1) & 1);
-        return rec[(size_t)((ii - 1) >> 1) * (size_t)ns64 + (size_t)((gl >> 4) * 64 + bg * 16 + (gl & 15))];
-      };
-      auto emit = [&](int op, int len) {
-        if (op == cur_op) {
-          cur_len += len;
-        } else {
-          if (cur_len > 0) {
-            if (x == 0) stg[nruns] = ((uint32_t)cur_len << 4) | (uint32_t)cur_op;
-            ++nruns;
-          }
-          cur_op = op;
-          cur_len = len;
-        }
-      };
-      while (!bad) {
-        if (state == 0) {
-          if (i == 0) {
-            if (EXT && j > 0) {  // an extension starts at the anchor: a leading deletion
-              emit(2, j);
-              j = 0;
-            }
-            break;
-          }
-          if (j == 0) {
-            if (LOCAL) break;
-            emit(1, i);  // a leading insertion (semi-global, extension)
-            i = 0;
-            break;
-          }
-          if (i > m_ || j > n_ || !in_band(i, j)) {
-            bad = true;
-            break;
-          }
-          if (LOCAL) {
-            int bit;
-            const uint32_t w = word(i, j, &bit);
-            if ((w >> (bit + 2)) & 1u) break;  // H = 0: the local alignment starts here
-          }
-          // lane x: the diagonal cells c = x + X * cc, (i - c, j - c), all on
-          // this lane's diagonal of the band
-          uint64_t good = 0, turn = 0, dl = 0;
-#pragma unroll
-          for (int cc = 0; cc < C; ++cc) {
-            const int c = x + X * cc;
-            const int ic = i - c, jc = j - c;
-            const bool in = ic >= 1 && jc >= 1;
-            bool diag = false, dlose = false, zero = false;
-            if (in) {
-              int bit;
-              const uint32_t w = word(ic, jc, &bit);
-              diag = ((w >> bit) & 1u) == 0;
-              dlose = ((w >> (bit + 16)) & 1u) != 0;
-              zero = LOCAL && ((w >> (bit + 2)) & 1u) != 0;
-            }
-            good |= sub(in && diag && !zero) << (X * cc);
-            turn |= sub(in && !diag && !zero) << (X * cc);
-            dl |= sub(dlose) << (X * cc);
-          }
-          const int Lr = first_clear_xc(good);
-          if (Lr > 0) {
-            emit(0, Lr);
-            i -= Lr;
-            j -= Lr;
-          }
-          // a cell that turns into a gap sets the state here; boundaries,
-          // range and the zero stop are left to the next iteration
-          if (Lr < XC && ((turn >> Lr) & 1u)) state = ((dl >> Lr) & 1u) ? 2 : 1;
-          continue;
-        }
-        if (i < 1 || j < 1 || i > m_ || j > n_) {
-          bad = true;
-          break;
-        }
-        if (state == 1) {
-          // a deletion along row i: cell (i, j - x) extends when the bit its
-          // left neighbour keeps says so; at column 1 a deletion can only open
-          const int jc = j - x;
-          bool ext = false;
-          if (jc >= 2 && in_band(i, jc - 1)) {
-            int bit;
-            const uint32_t w = word(i, jc - 1, &bit);
-            ext = ((w >> (bit + 1)) & 1u) != 0;
-          }
-          const int ones = first_clear(sub(ext));
-          if (ones < X) {  // cells 0..ones-1 extend, cell `ones` opens
-            emit(2, ones + 1);
-            j -= ones + 1;
-            state = 0;
-          } else {
-            emit(2, X);
-            j -= X;
-          }
-        } else {
-          // an insertion up column j: cell (i - x, j) extends when the bit of
-          // the cell above says so; at row 1 an insertion can only open
-          const int ic = i - x;
-          const bool in = ic >= 1;
-          bool ext = false;
-          if (ic >= 2 && in_band(ic - 1, j)) {
-            int bit;
-            const uint32_t w = word(ic - 1, j, &bit);
-            ext = ((w >> (bit + 17)) & 1u) != 0;
-          }
-          const int ones = first_clear(sub(ext));
-          const uint64_t inm = sub(in);
-          if (ones < X && ((inm >> ones) & 1u)) {
-            emit(1, ones + 1);
-            i -= ones + 1;
-            state = 0;
-          } else {
-            // X extensions, or a run that would leave the matrix (flagged
-            // by the range check of the next iteration)
-            emit(1, ones);
-            i -= ones;
-          }
-        }
-      }
-      if (cur_len > 0) {
-        if (x == 0) stg[nruns] = ((uint32_t)cur_len << 4) | (uint32_t)cur_op;
-        ++nruns;
-      }
-      if (bad) {
-        st |= kStInternal;
-        i = j = 0;
-        nruns = 0;
-      }
-      if (x == 0) {
-        if (prm->flags & (kOutStart | kOutCigar)) {
-          G(prm->read_start)[p_] = i;
-          G(prm->ref_start)[p_] = j;
-        }
-        if (prm->flags & kOutCigar) {
-          const int cap = prm->cigar_cap;
-          MICA_GLOBAL uint32_t* out = G(prm->cigar) + (size_t)p_ * (size_t)cap;
-          const int ncopy = nruns < cap ? nruns : cap;
-          for (int y = 0; y < ncopy; ++y) out[y] = stg[nruns - 1 - y];
-          if (nruns > cap) {
-            st |= kStCigarTrunc;
-            G(prm->n_cigar)[p_] = -nruns;
-          } else {
-            G(prm->n_cigar)[p_] = nruns;
-          }
-        }
-        G(prm->status)[p_] = st;
-      }
+      band_walk<V, MODE>(prm, rec, lds + q * kWalkStage, stg, ns64, p_, m_, n_, ie_, je_, dlo_, W_);
     }
   }
   lds_wait();

@@ -45,7 +45,12 @@ constexpr size_t kFbqstart = kSidehead + kNumBuckets;  // kNumBuckets + 1 entrie
 constexpr size_t kDbcount = kFbqstart + kNumBuckets + 8;
 constexpr size_t kDbwide = kDbcount + kNumBuckets;
 constexpr size_t kDbqstart = kDbwide + kNumBuckets;  // kNumBuckets + 1 entries
-constexpr size_t kWords = kDbqstart + kNumBuckets + 8;
+constexpr size_t kRcount = kDbqstart + kNumBuckets + 8;
+constexpr size_t kLcount = kRcount + kNumBuckets;
+constexpr size_t kNbcount = kLcount + kNumBuckets;
+constexpr size_t kWbcount = kNbcount + kNumBuckets;
+constexpr size_t kPqstart = kWbcount + kNumBuckets;  // kPruneParts * (kNumClasses + 1) entries
+constexpr size_t kWords = kPqstart + kPruneParts * (kNumClasses + 1) + 8;
 }  // namespace small
 
 // Work-queue order of the buckets (persistent parts first, each by
@@ -66,16 +71,55 @@ struct FillPlan {
   KernelFn fn[kMaxFills];
   int occ[kMaxFills];
   bool single[kMaxFills];  // one block of 256 threads without dynamic LDS (a scan between fills)
+  // side lists whose pairs k_seed_left takes whenever it has the waves for all
+  bool spare[kMaxFills];
   int n = 0;
   int occ_max = 1;
   int mode_mask = 0;  // modes the batch holds
+  // the seeded band launches before them (none: n_prune = 0): the scan, one
+  // band kernel per mode, and the shapes they share
+  KernelFn scan_fn;
+  int scan_threads = 256;   // a block's threads
+  size_t scan_shmem = 0;
+  KernelFn prune[kNumModes];
+  int prune_occ[kNumModes];
+  int n_prune = 0;
+  int prune_threads = 256;
+  size_t prune_shmem = 0;
+  KernelFn left[4];
+  int left_occ[4];
+  bool left_long_reads[4];
+  int n_left = 0;
+  int left_pairs = 2;  // pairs per item
+  Params prune_shape;       // the pr_ members only
 };
 mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch_t* b, const mica_scoring_t* s,
                          uint32_t flags, FillPlan* out);
 
-// Resident blocks per CU of a fill kernel (cached per device and kernel; no
-// device memory is allocated).
-mica_status_t kernel_occupancy(int device, KernelFn fn, int* blocks);
+// Resident blocks per CU of a kernel at a block shape (cached per device,
+// kernel and shape; no device memory is allocated).
+mica_status_t kernel_occupancy(int device, KernelFn fn, int threads, size_t shmem, int* blocks);
+
+// How many waves the band kernels of a plan may run with `bytes` of scratch
+// (a whole number of blocks, 0: not even one block), and the members of the
+// parameter block that follow.  `rerun`, `small`: the batch's re-run list
+// (free until the fills; it takes the planner's order) and table area.
+int64_t prune_slots(const FillPlan& fp, int n_cu, int64_t n_pairs, size_t bytes);
+void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_t fill_slots, uint32_t* rerun,
+                  uint32_t* small);
+
+// One kernel launch of a batch; `fill` marks the launches the timing events
+// bracket.
+struct Launch {
+  KernelFn fn;
+  unsigned grid, block;
+  size_t shmem;
+  bool fill;
+};
+// Every launch of a batch, in order.  slots: waves of the fills; pr_slots: of
+// the band kernels (0: none).
+void launch_sequence(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t slots, int64_t pr_slots,
+                     std::vector<Launch>* seq);
 
 // Bytes of one resident wave's scratch slot (direction words + CIGAR
 // staging) and its direction-word part; CIGAR staging words per pair.

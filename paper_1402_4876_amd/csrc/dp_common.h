@@ -94,6 +94,23 @@ __host__ __device__ constexpr int queue_part(int b) {
 
 constexpr uint32_t kSkip = 0xFFFFFFFFu;
 
+// The seeded band kernels (prune.h) take the packed 16-bit and the 32-bit
+// buckets, one kernel per kind and mode (a "prune part").  Their queue runs
+// through a part's classes from the longest reads to the shortest, whatever
+// the plan's lanes, so that neighbouring items hold reads of similar length.
+constexpr int kSeed = 12;  // bases of a read part: 24 bits, and 8 for its number
+static_assert(kMaxM / kSeed < 256, "a part's number fits beside its bases");
+constexpr int kPruneParts = 2 * kNumModes;
+constexpr int kPruneItem = 8;          // pairs per item of the scan
+constexpr int kScanChunk = 8;          // items a wave of the scan takes, at most
+constexpr int kScanStaticWords = 192 + 3 * kPruneItem * kScanChunk;  // LDS words of a wave before its sequences (scan)
+constexpr int kBandStaticWords = 64;   // and before its band codes (band)
+__host__ __device__ constexpr int prune_part(int kind, int mode) { return (kind == kK32 ? kNumModes : 0) + mode; }
+__host__ __device__ constexpr int prune_class(int pos) { return pos == 0 ? 16 : (pos == 1 ? 18 : (pos == 2 ? 17 : 18 - pos)); }
+// classes whose left pairs k_seed_left takes always (else: while they are few)
+__host__ __device__ constexpr bool left_long(int cls) { return class_lanes(cls) * class_rows(cls) > 256; }
+__host__ __device__ constexpr bool prune_kind(int kind) { return kind != kK16Sat; }
+
 // counters[] slots
 // (queue heads of the persistent kernels: kCtrQueueHead + queue part)
 // (queue heads of the persistent side-list kernels: kCtrSideHead + queue part)
@@ -103,7 +120,12 @@ enum : int {
   kCtrItems,
   kCtrRerunHead,
   kCtrSideHead,
-  kNumCounters = kCtrSideHead + kPersistParts
+  kCtrPruneWide = kCtrSideHead + kPersistParts,  // pairs the band kernels finished or left to the full
+  kCtrPruneMid,                                 // traceback, by band width: over 64 diagonals, 17-64
+  kCtrPruneLeft,                                // pairs left to the full traceback
+  kCtrSeedTried,                                // scanned pairs of the items that report, and the
+  kCtrSeedFound,                                // ones of them answered or listed
+  kNumCounters
 };
 
 // per-pair status bits (same values as the public header)
@@ -202,6 +224,24 @@ struct Params {
   uint64_t dir_bytes;          // direction-bit part of a slot
   int32_t stage_stride;        // CIGAR staging words per pair
   int32_t n_slots;             // resident waves the scratch is sized for
+  // seeded band kernels (unused when presorted is NULL)
+  uint32_t* presorted;         // [n_pairs] the planner's order; what they leave goes to `sorted`
+  uint32_t* rcount;            // [kNumBuckets] pairs left per bucket
+  uint32_t* lcount;            // [kNumBuckets] pairs left to k_seed_left
+  int32_t left_waves;          // waves of its short-read launches (0: there are none)
+  uint32_t* nbcount;           // [kNumBuckets] pairs on the band lists, one strip
+  uint32_t* wbcount;           // [kNumBuckets] and more
+  uint32_t* pqstart;           // [kPruneParts][kNumClasses + 1] first queue item of each class
+  uint64_t pr_slot_bytes, pr_rec_bytes;  // a wave's part of scratch, its band records
+  int32_t pr_slots;
+  int32_t pr_chunk;            // items per wave of the scan
+  int32_t pr_scan_words, pr_band_words;  // LDS words per wave
+  int32_t pr_win_words, pr_read_words, pr_part_words;  // scan: LDS words per pair
+  int32_t pr_rows, pr_group_words;                     // band: rows, LDS words per group
+  int32_t pr_raw_off, pr_raw_words;                    // and of its sequences
+  // twice the least loss that spoils a read part, and the same beside a gap
+  int32_t pr_cost2, pr_cost2_local, pr_leave2, pr_leave2_local;
+  int32_t pr_move2_del, pr_move2_ins;  // the same beside a run that may be split
   uint32_t persist_q[kQueueParts];  // queue positions [persist_q[q], persist_q[q+1]) of queue part q
 };
 
@@ -218,6 +258,11 @@ struct KernelTable {
   KernelFn side[kNumBuckets];
   KernelFn side_persistent[kNumModes][2];
   KernelFn sidescan;
+  KernelFn seed_scan[2][2];             // [with traceback][32-bit]
+  KernelFn seed_band[2][2][kNumModes];  // [with traceback][32-bit][mode]
+  KernelFn seed_left[2][2][2];          // [32-bit][mode][long reads]
+  KernelFn rescan;                      // after them
+  KernelFn front;                       // zero, plan, scan and scatter of a small batch
   KernelFn rerun[2];
   KernelFn zero, plan, scan, scatter;
   KernelTable();

@@ -113,6 +113,7 @@ struct V32 {
   __device__ static T vmax(T a, T b) { return a > b ? a : b; }
   __device__ static T vmin(T a, T b) { return a < b ? a : b; }
   __device__ static T max3(T a, T b, T c) { return vmax(vmax(a, b), c); }
+  __device__ static T negmask(T d) { return d >> 31; }
   // sign bytes b, b, a, a (the byte layout of the 16-bit variant, half 1 a copy of half 0)
   static constexpr uint32_t kSignSel = 0x0B0B0909u;
   __device__ static T splat(int v) { return v; }
@@ -731,6 +732,9 @@ __device__ __forceinline__ void process_item(const Params* __restrict__ prm,
   constexpr int X = P / NP;
   const int h = k / X;
   const int x = k - h * X;
+  // (pairs the seeded band kernels left come here without a banded fill)
+  const bool left = TB == kTbFull && MODE != 2 && !SAT && bucket >= 0 && prm->presorted != nullptr;
+  BandCount width{0, 0};
   if (g * NP + h < npairs) {
     // the pair's parameters are read again here rather than kept in
     // registers across the fill loop
@@ -756,6 +760,7 @@ __device__ __forceinline__ void process_item(const Params* __restrict__ prm,
         G(prm->score)[p_] = score;
         G(prm->read_end)[p_] = ie;
         G(prm->ref_end)[p_] = je;
+        if (left) band_count<V, MODE>(prm, m_, n_, 0, score, ie, je, &width);
       }
       uint32_t st = 0;
       if constexpr (DIR) {
@@ -986,6 +991,7 @@ __device__ __forceinline__ void process_item(const Params* __restrict__ prm,
       if (x == 0) G(prm->status)[p_] = st;
     }
   }
+  if (left) band_count_flush(prm, width);
   lds_wait();
 }
 

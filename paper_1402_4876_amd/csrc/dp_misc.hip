@@ -32,7 +32,7 @@ __global__ __launch_bounds__(256) void k_rerun(const Params* __restrict__ prm) {
 // ----------------------------------------------------------------------------
 // planning: validation, trivial pairs, bucket histogram, work queue
 
-__global__ void k_zero(const Params* __restrict__ prm) {
+__device__ __forceinline__ void zero_tables(const Params* __restrict__ prm) {
   for (int i = threadIdx.x; i < kNumSubBuckets; i += blockDim.x) prm->scount[i] = 0;
   const int i = threadIdx.x;
   if (i < kNumBuckets) {
@@ -44,6 +44,8 @@ __global__ void k_zero(const Params* __restrict__ prm) {
   }
   if (i < kNumCounters) prm->counters[i] = 0;
 }
+
+__global__ void k_zero(const Params* __restrict__ prm) { zero_tables(prm); }
 
 // Can every value of the pair's DP stay inside int16 (with a guard band)?
 // Semi-global and local values are shifted by -d0 (dummy rows above the
@@ -65,68 +67,73 @@ __device__ __forceinline__ bool int16_safe(int m, int n, int mode, int d0, int a
   return hi <= 32767 - 8 && lo >= -32767 + 8;
 }
 
+// One pair: validation, and the result at once where there is nothing to
+// align; else its bucket and length bin (counted in hist), kSkip otherwise.
+__device__ __forceinline__ uint32_t plan_pair(const Params* __restrict__ prm, int64_t p, uint32_t* hist) {
+  const int m = prm->read_len[p], n = prm->win_len[p];
+  const int md = prm->mode ? (int)prm->mode[p] : prm->default_mode;
+  const uint64_t wo = prm->win_off[p], ro = prm->read_off[p];
+  const int h0 = md == 2 ? (prm->ext_h0 ? prm->ext_h0[p] : prm->ext_default_h0) : 0;
+  uint32_t st = 0;
+  if (m < prm->min_m || n < 0 || m > prm->max_m || n > prm->max_n || md < 0 || md > 2 || !((prm->mode_mask >> md) & 1) ||
+      h0 < 0 || h0 > prm->max_h0)
+    st = kStLenLimit;
+  else if (wo > prm->ref_len || (uint64_t)n > prm->ref_len - wo) st = kStWinOob;
+  else if (ro > prm->reads_len || (uint64_t)m > prm->reads_len - ro) st = kStReadOob;
+  const bool want_start = (prm->flags & (kOutStart | kOutCigar)) != 0;
+  const bool want_cigar = (prm->flags & kOutCigar) != 0;
+  uint32_t b = kSkip;
+  if (st != 0 || m == 0 || n == 0) {
+    int score = 0, re = 0;
+    int ncig = 0;
+    // semi-global against an empty window: all insertions; an extension
+    // with an empty read or window: the anchor itself, or (empty window)
+    // all insertions when that is within the clipping penalty
+    const bool all_ins = st == 0 && m > 0 &&
+                         (md == 0 || (md == 2 && (long)prm->so + (long)m * prm->se <= (long)prm->ext_clip));
+    if (st == 0 && md == 2) score = h0;
+    if (all_ins) {
+      score = (md == 2 ? h0 : 0) - (prm->so + m * prm->se);
+      re = m;
+      ncig = 1;
+      if (want_cigar) {
+        if (prm->cigar_cap >= 1) prm->cigar[(size_t)p * prm->cigar_cap] = ((uint32_t)m << 4) | 1u;
+        else st |= kStCigarTrunc;
+      }
+    }
+    prm->score[p] = score;
+    prm->read_end[p] = re;
+    prm->ref_end[p] = 0;
+    if (want_start) {
+      prm->read_start[p] = 0;
+      prm->ref_start[p] = 0;
+    }
+    if (want_cigar) prm->n_cigar[p] = (st & kStCigarTrunc) ? -ncig : ncig;
+    prm->status[p] = st;
+  } else {
+    const int cls = prm->class_of_m[m];
+    const int d0 = class_lanes(cls) * class_rows(cls) - m;
+    // the 16-bit bounds hold for the fallback class's dummy rows too
+    // (at least as many as the pair's own class)
+    const int fbc = fallback_class(cls);
+    const int d0k = class_lanes(fbc) * class_rows(fbc) - m;
+    int kind;
+    if (prm->flags & kForceInt32) kind = kK32;
+    else kind = int16_safe(m, n, md, d0k, prm->sa, prm->sb, prm->so, prm->se, h0) ? kK16 : kK16Sat;
+    b = (uint32_t)(bucket_id(kind, cls, md) * kSubBins + sub_bin(cls, d0));
+    atomicAdd(&hist[b], 1u);
+  }
+  prm->bucket_of[p] = b;
+  return b;
+}
+
 __global__ __launch_bounds__(kPlanThreads) void k_plan(const Params* __restrict__ prm) {
   __shared__ uint32_t hist[kNumSubBuckets];
   for (int i = threadIdx.x; i < kNumSubBuckets; i += blockDim.x) hist[i] = 0;
   __syncthreads();
   for (int rep = 0; rep < kPlanPairsPerThread; ++rep) {
     const int64_t p = ((int64_t)blockIdx.x * kPlanPairsPerThread + rep) * blockDim.x + threadIdx.x;
-    if (p < prm->n_pairs) {
-      const int m = prm->read_len[p], n = prm->win_len[p];
-      const int md = prm->mode ? (int)prm->mode[p] : prm->default_mode;
-      const uint64_t wo = prm->win_off[p], ro = prm->read_off[p];
-      const int h0 = md == 2 ? (prm->ext_h0 ? prm->ext_h0[p] : prm->ext_default_h0) : 0;
-      uint32_t st = 0;
-      if (m < prm->min_m || n < 0 || m > prm->max_m || n > prm->max_n || md < 0 || md > 2 || !((prm->mode_mask >> md) & 1) ||
-          h0 < 0 || h0 > prm->max_h0)
-        st = kStLenLimit;
-      else if (wo > prm->ref_len || (uint64_t)n > prm->ref_len - wo) st = kStWinOob;
-      else if (ro > prm->reads_len || (uint64_t)m > prm->reads_len - ro) st = kStReadOob;
-      const bool want_start = (prm->flags & (kOutStart | kOutCigar)) != 0;
-      const bool want_cigar = (prm->flags & kOutCigar) != 0;
-      uint32_t b = kSkip;
-      if (st != 0 || m == 0 || n == 0) {
-        int score = 0, re = 0;
-        int ncig = 0;
-        // semi-global against an empty window: all insertions; an extension
-        // with an empty read or window: the anchor itself, or (empty window)
-        // all insertions when that is within the clipping penalty
-        const bool all_ins = st == 0 && m > 0 &&
-                             (md == 0 || (md == 2 && (long)prm->so + (long)m * prm->se <= (long)prm->ext_clip));
-        if (st == 0 && md == 2) score = h0;
-        if (all_ins) {
-          score = (md == 2 ? h0 : 0) - (prm->so + m * prm->se);
-          re = m;
-          ncig = 1;
-          if (want_cigar) {
-            if (prm->cigar_cap >= 1) prm->cigar[(size_t)p * prm->cigar_cap] = ((uint32_t)m << 4) | 1u;
-            else st |= kStCigarTrunc;
-          }
-        }
-        prm->score[p] = score;
-        prm->read_end[p] = re;
-        prm->ref_end[p] = 0;
-        if (want_start) {
-          prm->read_start[p] = 0;
-          prm->ref_start[p] = 0;
-        }
-        if (want_cigar) prm->n_cigar[p] = (st & kStCigarTrunc) ? -ncig : ncig;
-        prm->status[p] = st;
-      } else {
-        const int cls = prm->class_of_m[m];
-        const int d0 = class_lanes(cls) * class_rows(cls) - m;
-        // the 16-bit bounds hold for the fallback class's dummy rows too
-        // (at least as many as the pair's own class)
-        const int fbc = fallback_class(cls);
-        const int d0k = class_lanes(fbc) * class_rows(fbc) - m;
-        int kind;
-        if (prm->flags & kForceInt32) kind = kK32;
-        else kind = int16_safe(m, n, md, d0k, prm->sa, prm->sb, prm->so, prm->se, h0) ? kK16 : kK16Sat;
-        b = (uint32_t)(bucket_id(kind, cls, md) * kSubBins + sub_bin(cls, d0));
-        atomicAdd(&hist[b], 1u);
-      }
-      prm->bucket_of[p] = b;
-    }
+    if (p < prm->n_pairs) (void)plan_pair(prm, p, hist);
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kNumSubBuckets; i += blockDim.x)
@@ -139,24 +146,31 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const Params* __restrict_
 constexpr int kScanThreads = 256;
 static_assert(kNumBuckets <= kScanThreads, "one thread per bucket");
 
-// exclusive prefix sum over the block (Hillis-Steele in LDS); *total gets the sum
+// exclusive prefix sum over the block (within the waves by shuffles, their
+// sums through sh); *total gets the sum
 __device__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t* total) {
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int d = 1; d < kScanThreads; d <<= 1) {
-    const uint32_t x = t >= d ? sh[t - d] : 0u;
-    __syncthreads();
-    sh[t] += x;
-    __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t incl = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
   }
-  const uint32_t incl = sh[t];
-  *total = sh[kScanThreads - 1];
+  if (lane == 63) sh[wave] = incl;
   __syncthreads();
-  return incl - v;
+  uint32_t before = 0, sum = 0;
+#pragma unroll
+  for (int w = 0; w < kScanThreads / 64; ++w) {
+    const uint32_t x = sh[w];
+    before += w < wave ? x : 0u;
+    sum += x;
+  }
+  *total = sum;
+  __syncthreads();
+  return before + incl - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan(const Params* __restrict__ prm) {
+__device__ __forceinline__ void scan_tables(const Params* __restrict__ prm) {
   __shared__ uint32_t cnt[kNumBuckets];
   __shared__ uint32_t sh[kScanThreads];
   const int b = threadIdx.x;
@@ -188,6 +202,27 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(const Params* __restrict_
 #pragma unroll
     for (int s = 0; s < kSubBins; ++s) prm->sfill[b * kSubBins + s] = start + sub[s];
   }
+  if (prm->presorted) {
+    // the band kernels' queue: thread = (part, class position)
+    const int part = b / kNumClasses, pos = b - part * kNumClasses;
+    const bool in = part < kPruneParts;
+    uint32_t pi = 0;
+    if (in) {
+      const int bq = bucket_id(part < kNumModes ? kK16 : kK32, prune_class(pos), part % kNumModes);
+      pi = (cnt[bq] + kPruneItem - 1) / kPruneItem;
+    }
+    uint32_t all;
+    const uint32_t ps = block_exclusive_scan(pi, sh, &all);
+    if (in) {
+      prm->pqstart[part * (kNumClasses + 1) + pos] = ps;
+      if (pos == kNumClasses - 1) prm->pqstart[part * (kNumClasses + 1) + kNumClasses] = ps + pi;
+    }
+    if (b < kNumBuckets) {
+      prm->rcount[b] = prune_kind(bucket_kind(b)) ? 0u : acc;
+      prm->nbcount[b] = 0;
+      prm->wbcount[b] = 0;
+    }
+  }
   if (b == 0) {
     prm->qstart[kNumBuckets] = n_items;
     prm->counters[kCtrItems] = n_items;
@@ -197,11 +232,12 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(const Params* __restrict_
   (void)n_sorted;
 }
 
+__global__ __launch_bounds__(kScanThreads) void k_scan(const Params* __restrict__ prm) { scan_tables(prm); }
+
 // After the banded fills: the first work item of every queue position of
 // the persistent buckets in the two side lists of the fills (fb: bands too
 // wide for the refill; db: bands of 17-64 diagonals).
-__global__ __launch_bounds__(kScanThreads) void k_sidescan(const Params* __restrict__ prm) {
-  __shared__ uint32_t sh[kScanThreads];
+__device__ __forceinline__ void sidescan_tables(const Params* __restrict__ prm, uint32_t* sh) {
   const int q = threadIdx.x;
 #pragma unroll 1
   for (int list = 0; list < 2; ++list) {
@@ -222,6 +258,54 @@ __global__ __launch_bounds__(kScanThreads) void k_sidescan(const Params* __restr
     if (q == 0) qstart[kNumBuckets] = total;
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_sidescan(const Params* __restrict__ prm) {
+  __shared__ uint32_t sh[kScanThreads];
+  sidescan_tables(prm, sh);
+}
+
+// After the band kernels: bucket sizes and queue of the pairs they left, to
+// the fills or to the full traceback.
+__global__ __launch_bounds__(kScanThreads) void k_rescan(const Params* __restrict__ prm) {
+  __shared__ uint32_t sh[kScanThreads];
+  const int q = threadIdx.x;
+  // (see left_list of the band kernels)
+  const bool traced = (prm->flags & (kOutStart | kOutCigar)) != 0;
+  auto full = [&](int b) { return traced && prune_kind(bucket_kind(b)) && bucket_mode(b) != 2; };
+  // few enough for the kernel that takes them a wave each?
+  uint32_t waves = 0, all_waves;
+  if (q < kNumBuckets && full(q) && !left_long(bucket_class(q))) {
+    const uint32_t per = bucket_kind(q) == kK32 ? 1u : 2u;
+    waves = (prm->rcount[q] + per - 1) / per;
+  }
+  (void)block_exclusive_scan(waves, sh, &all_waves);
+  const bool few = all_waves <= 4u * (uint32_t)prm->left_waves;
+  uint32_t items = 0, left = 0;
+  if (q < kNumBuckets) {
+    const int bq = (int)prm->qorder[q];
+    const uint32_t ppi = (uint32_t)pairs_per_item(bucket_kind(bq), bucket_class(bq));
+    items = full(bq) ? 0u : (prm->rcount[bq] + ppi - 1) / ppi;
+    left = full(q) ? prm->rcount[q] : 0u;
+    prm->bcount[q] = full(q) ? 0u : prm->rcount[q];
+    const bool mine = full(q) && (few || left_long(bucket_class(q)));
+    prm->lcount[q] = mine ? left : 0u;
+    if (full(q)) prm->fbcount[q] = mine ? 0u : left;
+    if (mine) left = 0;  // (not among fbcount's)
+  }
+  uint32_t n_items, n_left;
+  const uint32_t qs = block_exclusive_scan(items, sh, &n_items);
+  (void)block_exclusive_scan(left, sh, &n_left);
+  if (q < kNumBuckets) prm->qstart[q] = qs;
+  if (q == 0) {
+    prm->qstart[kNumBuckets] = n_items;
+    prm->counters[kCtrItems] = n_items;
+    prm->counters[kCtrPruneLeft] = n_left;
+  }
+  // (a batch without extensions has no fill between here and the side lists)
+  __syncthreads();
+  __threadfence_block();
+  sidescan_tables(prm, sh);
 }
 
 __global__ __launch_bounds__(kPlanThreads) void k_scatter(const Params* __restrict__ prm) {
@@ -247,7 +331,38 @@ __global__ __launch_bounds__(kPlanThreads) void k_scatter(const Params* __restri
 #pragma unroll
   for (int rep = 0; rep < kPlanPairsPerThread; ++rep) {
     const int64_t p = ((int64_t)blockIdx.x * kPlanPairsPerThread + rep) * blockDim.x + threadIdx.x;
-    if (b[rep] != kSkip) prm->sorted[base[b[rep]] + rank[rep]] = (uint32_t)p;
+    if (b[rep] != kSkip) {
+      uint32_t* to = prm->presorted && prune_kind(bucket_kind((int)b[rep] / kSubBins)) ? prm->presorted : prm->sorted;
+      to[base[b[rep]] + rank[rep]] = (uint32_t)p;
+    }
+  }
+}
+
+// A small batch (at most kFrontPairs pairs): clearing, planning, scans and
+// scatter in one block, in place of four launches (each some 5 us of start
+// and drain for less than 1 us of work).
+__global__ __launch_bounds__(kScanThreads) void k_front(const Params* __restrict__ prm) {
+  __shared__ uint32_t hist[kNumSubBuckets];
+  const int n = (int)prm->n_pairs;
+  zero_tables(prm);
+  for (int i = threadIdx.x; i < kNumSubBuckets; i += kScanThreads) hist[i] = 0;
+  __syncthreads();
+  for (int p = threadIdx.x; p < n; p += kScanThreads) (void)plan_pair(prm, p, hist);
+  __syncthreads();
+  for (int i = threadIdx.x; i < kNumSubBuckets; i += kScanThreads) prm->scount[i] = hist[i];
+  __threadfence();
+  __syncthreads();
+  scan_tables(prm);
+  __threadfence();
+  __syncthreads();
+  for (int i = threadIdx.x; i < kNumSubBuckets; i += kScanThreads)
+    if (hist[i]) hist[i] = prm->sfill[i];
+  __syncthreads();
+  for (int p = threadIdx.x; p < n; p += kScanThreads) {
+    const uint32_t b = prm->bucket_of[p];
+    if (b == kSkip) continue;
+    uint32_t* to = prm->presorted && prune_kind(bucket_kind((int)b / kSubBins)) ? prm->presorted : prm->sorted;
+    to[atomicAdd(&hist[b], 1u)] = (uint32_t)p;
   }
 }
 
@@ -289,7 +404,23 @@ MICA_PERSIST_ALL(MICA_PERSIST_DECL)
 #define MICA_PERSIST_SIDE_DECL(mode, part) void reg_persistent_side_##mode##_##part(KernelTable& t);
 MICA_PERSIST_SIDE_ALL(MICA_PERSIST_SIDE_DECL)
 
+#define MICA_SEED_ALL(X) \
+  X(0, 0, 0) X(0, 0, 1) X(0, 0, 2) X(0, 1, 0) X(0, 1, 1) X(0, 1, 2) \
+  X(1, 0, 0) X(1, 0, 1) X(1, 0, 2) X(1, 1, 0) X(1, 1, 1) X(1, 1, 2)
+#define MICA_SEED_DECL(tb, wide, mode) void reg_seed_##tb##_##wide##_##mode(KernelTable& t);
+MICA_SEED_ALL(MICA_SEED_DECL)
+
+#define MICA_LEFT_ALL(X) X(0, 0, 0) X(0, 0, 1) X(0, 1, 0) X(0, 1, 1) X(1, 0, 0) X(1, 0, 1) X(1, 1, 0) X(1, 1, 1)
+#define MICA_LEFT_DECL(wide, mode, lng) void reg_seed_left_##wide##_##mode##_##lng(KernelTable& t);
+#define MICA_LEFT_CALL(wide, mode, lng) reg_seed_left_##wide##_##mode##_##lng(*this);
+MICA_LEFT_ALL(MICA_LEFT_DECL)
+
 KernelTable::KernelTable() {
+#define MICA_SEED_CALL(tb, wide, mode) reg_seed_##tb##_##wide##_##mode(*this);
+  MICA_SEED_ALL(MICA_SEED_CALL)
+  rescan = &k_rescan;
+  MICA_LEFT_ALL(MICA_LEFT_CALL)
+  front = &k_front;
 #define MICA_FILL_CALL(kind, mode, dir) reg_fill_##kind##_##mode##_##dir(*this);
   MICA_FILL_ALL(MICA_FILL_CALL)
 #define MICA_SIDE_CALL(kind, mode) reg_side_##kind##_##mode(*this);

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <vector>
 
 #include "ctx.h"
 #include "dp_common.h"
@@ -157,21 +158,15 @@ mica_status_t mica_dp_align_batch_noalloc(const mica_batch_t* b, const mica_scor
   P.stage_stride = sh.stage_stride;
   P.n_slots = (int32_t)slots;
   queue_order(a.qorder, P.persist_q);
+  const int64_t pr_waves = prune_slots(fp, ds.n_cu, b->n_pairs, area);
+  if (pr_waves > 0) prune_params(&P, fp, ds.n_cu, pr_waves, slots, P.rerun, sm);
   const Params* dp = (const Params*)(ds.base + kOffParams);
 
   hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(256), 0, stream, a, ds.base);
   HIP_TRY(hipGetLastError());
-  const KernelTable& K = kernels();
-  const unsigned pblocks = (unsigned)((b->n_pairs + kPlanPairsPerBlock - 1) / kPlanPairsPerBlock);
-  HIP_TRY(launch(K.zero, 1, 256, 0, stream, dp));
-  HIP_TRY(launch(K.plan, pblocks, kPlanThreads, 0, stream, dp));
-  HIP_TRY(launch(K.scan, 1, 256, 0, stream, dp));
-  HIP_TRY(launch(K.scatter, pblocks, kPlanThreads, 0, stream, dp));
-  for (int i = 0; i < fp.n; ++i) {
-    const int64_t blocks = std::min<int64_t>((int64_t)fp.occ[i] * ds.n_cu, slots / kWavesPerBlock);
-    if (fp.single[i]) HIP_TRY(launch(fp.fn[i], 1, 256, 0, stream, dp));
-    else HIP_TRY(launch(fp.fn[i], (unsigned)std::max<int64_t>(blocks, 1), 256, kFillShmem, stream, dp));
-  }
+  std::vector<Launch> seq;
+  launch_sequence(fp, ds.n_cu, b->n_pairs, slots, pr_waves, &seq);
+  for (const Launch& l : seq) HIP_TRY(launch(l.fn, l.grid, l.block, l.shmem, stream, dp));
   return MICA_OK;
 }
 

@@ -9,4 +9,6 @@ namespace mica {
 constexpr int kPlanThreads = 256;
 constexpr int kPlanPairsPerThread = 4;
 constexpr int kPlanPairsPerBlock = kPlanThreads * kPlanPairsPerThread;
+// batches up to this size are planned by one block
+constexpr int kFrontPairs = 1024;
 }  // namespace mica

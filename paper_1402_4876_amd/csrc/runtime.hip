@@ -133,15 +133,6 @@ hipError_t launch(KernelFn fn, unsigned blocks, unsigned threads, size_t shmem, 
   return hipLaunchKernel((const void*)fn, dim3(blocks), dim3(threads), args, shmem, s);
 }
 
-// One kernel launch of a batch; `fill` marks the launches the timing events
-// bracket.
-struct Launch {
-  KernelFn fn;
-  unsigned grid, block;
-  size_t shmem;
-  bool fill;
-};
-
 hipKernelNodeParams node_params(const Launch& l, void** args) {
   hipKernelNodeParams p;
   std::memset(&p, 0, sizeof(p));
@@ -279,6 +270,8 @@ namespace {
 struct OccEntry {
   int device;
   KernelFn fn;
+  int threads;
+  size_t shmem;
   int blocks;
 };
 constexpr int kOccCache = 1024;
@@ -287,19 +280,229 @@ int g_n_occ = 0;
 std::mutex g_occ_mu;
 }  // namespace
 
-mica_status_t kernel_occupancy(int device, KernelFn fn, int* blocks) {
+mica_status_t kernel_occupancy(int device, KernelFn fn, int threads, size_t shmem, int* blocks) {
   std::lock_guard<std::mutex> g(g_occ_mu);
   for (int i = 0; i < g_n_occ; ++i)
-    if (g_occ[i].device == device && g_occ[i].fn == fn) {
+    if (g_occ[i].device == device && g_occ[i].fn == fn && g_occ[i].threads == threads && g_occ[i].shmem == shmem) {
       *blocks = g_occ[i].blocks;
       return MICA_OK;
     }
   int nb = 0;
-  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)fn, 256, kFillShmem));
+  HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)fn, threads, shmem));
   nb = std::max(nb, 1);
-  if (g_n_occ < kOccCache) g_occ[g_n_occ++] = {device, fn, nb};
+  if (g_n_occ < kOccCache) g_occ[g_n_occ++] = {device, fn, threads, shmem, nb};
   *blocks = nb;
   return MICA_OK;
+}
+
+namespace {
+
+// Twice the least loss per spoiled read part (prune.h): a substitution or a
+// deletion spoils one part; an insertion run of L bases that touches s parts
+// has L >= 1, 2, 2 + (s - 2) kSeed, ... and costs o + L (a + e) for the s.
+int spoil_cost2(const mica_scoring_t& s) {
+  int c2 = 2 * std::min(s.match - s.mismatch, s.gap_open + s.gap_extend);
+  for (int k = 1; k <= kMaxM / kSeed; ++k) {
+    const int len = k <= 2 ? k : 2 + (k - 2) * kSeed;
+    c2 = std::min(c2, 2 * (s.gap_open + len * (s.match + s.gap_extend)) / k);
+  }
+  return c2;
+}
+
+// The band kernels of a batch.  Plain launches compute every table in full
+// (they are what the band kernels are compared with), and reads too short
+// for a certificate only pay for the scan.
+mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch_t* b, const mica_scoring_t& s, uint32_t flags, int traced,
+                         const bool any_mode[kNumModes], FillPlan* fp) {
+  fp->n_prune = 0;
+  if (flags & MICA_PLAIN_LAUNCH) return MICA_OK;
+  // Scores alone take one pass of the fill: where that does not fill the GPU
+  // several times over, one item's latency is the time of both ways (1,000
+  // pairs of 150 x 200 in 32 bits: 60 us in the fill, 170 us here).
+  if (!traced && b->n_pairs < 65536) return MICA_OK;
+  // two parts at least to hope for an answer (local: three), four where that
+  // saves no traceback
+  const int parts = b->max_read_len / kSeed;
+  if (!any_mode[MICA_MODE_EXTEND] && parts < (traced ? (any_mode[MICA_MODE_SEMIGLOBAL] ? 2 : 3) : 4)) return MICA_OK;
+  // (the pairs left run in up to 256 dummy rows, more than the planner's 16-bit
+  // check of short reads allows for)
+  if (!(flags & MICA_FORCE_INT32) && 2L * s.gap_open + (long)(kMaxM + 1) * s.gap_extend + 256 > 32767 - 8) return MICA_OK;
+  Params& S = fp->prune_shape;
+  std::memset(&S, 0, sizeof(S));
+  const int m = b->max_read_len, n = b->max_win_len;
+  S.pr_cost2 = spoil_cost2(s);
+  S.pr_cost2_local = std::min(S.pr_cost2, 2 * kSeed * s.match);
+  // off the diagonal, next to the gap that led there: an inserted run may have
+  // spoiled whole parts, each with its kSeed bases
+  S.pr_leave2 = std::min(S.pr_cost2, 2 * kSeed * (s.match + s.gap_extend));
+  S.pr_leave2_local = std::min(S.pr_cost2_local, S.pr_leave2);
+  // (a clipped end spoils its further parts with kSeed bases each)
+  const int move2 = std::min(S.pr_leave2, 2 * kSeed * s.match);
+  S.pr_move2_del = std::min(move2, 2 * s.gap_open);
+  S.pr_move2_ins = std::min(move2, s.gap_open);
+  S.pr_win_words = (n + 15) / 16 + 2;
+  S.pr_read_words = (m + 15) / 16 + 1;
+  S.pr_part_words = std::max(4, (m / kSeed + 3) / 4 * 4);
+  S.pr_rows = (m + 1) / 2 * 2;
+  S.pr_group_words = S.pr_rows + (m + kBandMaxW + 2) / 2;
+  S.pr_scan_words = kScanStaticWords + 8 * (S.pr_win_words + S.pr_read_words + S.pr_part_words);
+  // (sequences of the two pairs of a group: read and band, from any base)
+  S.pr_raw_off = kBandStaticWords + (int)align_up((size_t)4 * S.pr_group_words, 4);
+  S.pr_raw_words = 2 * ((m + 15) / 16 + (m + kBandMaxW + 15) / 16);
+  S.pr_band_words = S.pr_raw_off + (int)align_up((size_t)4 * S.pr_raw_words, 4);
+  // direction bits of up to 4 strips, two rows a word; CIGAR staging of 8 pairs
+  S.pr_rec_bytes = traced ? (uint64_t)(m / 2 + 1) * 1024 : 0;
+  S.pr_slot_bytes = std::max<uint64_t>(
+      align_up(S.pr_rec_bytes + (traced ? (size_t)8 * (size_t)(m + n + 2) * 4 : 0), 256), 256);
+  // blocks of four waves, or fewer where their LDS would pass 64 KB (rounded,
+  // so that batches of similar bounds share their launch graph)
+  auto block = [](int words, int* threads, size_t* shmem) {
+    const size_t bytes = (size_t)words * 4;
+    *threads = bytes * 4 <= (size_t)65536 ? 256 : (bytes * 2 <= (size_t)65536 ? 128 : 64);
+    *shmem = align_up(bytes * (size_t)(*threads / 64), 2048);
+  };
+  block(S.pr_scan_words, &fp->scan_threads, &fp->scan_shmem);
+  block(S.pr_band_words, &fp->prune_threads, &fp->prune_shmem);
+  const int wide = (flags & MICA_FORCE_INT32) ? 1 : 0;
+  fp->scan_fn = kernels().seed_scan[traced][wide];
+  int n_prune = 0;
+  for (int md = 0; md < kNumModes; ++md) {
+    if (!any_mode[md]) continue;
+    fp->prune[n_prune] = kernels().seed_band[traced][wide][md];
+    mica_status_t st =
+        kernel_occupancy(device, fp->prune[n_prune], fp->prune_threads, fp->prune_shmem, &fp->prune_occ[n_prune]);
+    if (st != MICA_OK) return st;
+    ++n_prune;
+  }
+  fp->n_prune = n_prune;
+  fp->n_left = 0;
+  fp->left_pairs = wide ? 1 : 2;
+  for (int md = 0; md < 2 && traced; ++md)
+    for (int lng = 0; lng < 2; ++lng) {
+      bool used = false;
+      for (int r = std::max(1, b->min_read_len); r <= m; ++r) used |= (left_long(class_of_m[r]) ? 1 : 0) == lng;
+      if (!any_mode[md] || !used) continue;
+      const int i = fp->n_left++;
+      fp->left[i] = kernels().seed_left[wide][md][lng];
+      fp->left_long_reads[i] = lng;
+      mica_status_t st = kernel_occupancy(device, fp->left[i], 256, kFillShmem, &fp->left_occ[i]);
+      if (st != MICA_OK) return st;
+    }
+  return MICA_OK;
+}
+
+}  // namespace
+
+int64_t prune_slots(const FillPlan& fp, int n_cu, int64_t n_pairs, size_t bytes) {
+  if (fp.n_prune == 0) return 0;
+  const int64_t per_block = fp.prune_threads / 64;
+  int occ = 1;
+  for (int i = 0; i < fp.n_prune; ++i) occ = std::max(occ, fp.prune_occ[i]);
+  int64_t slots = (int64_t)occ * n_cu * per_block;
+  // the bands of a mode: at most one partial item per class and list
+  slots = std::min(slots, (int64_t)align_up((size_t)(n_pairs / 4 + 2 * kNumClasses), (size_t)per_block));
+  // (a slot here is no larger than a fill's, so memory for a block of fills,
+  // without which the call fails, holds a block of these)
+  return std::min(slots, (int64_t)(bytes / fp.prune_shape.pr_slot_bytes) / per_block * per_block);
+}
+
+// Items a wave of the scan takes: about two waves per SIMD, so that what the
+// first items of a batch of unrelated pairs gave spares it the others, and at
+// least one list request per kScanChunk items.
+static int scan_chunk(int n_cu, int64_t n_pairs) {
+  const int64_t per_wave = n_pairs / kPruneItem / ((int64_t)n_cu * 8);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kScanChunk, per_wave));
+}
+
+// the waves of a k_seed_left launch: an item each, as far as they are resident
+static int64_t left_waves(const FillPlan& fp, int i, int n_cu, int64_t n_pairs, int64_t fill_slots) {
+  const int64_t items = n_pairs / fp.left_pairs + kNumClasses;  // a partial one per class
+  const int64_t want = std::min<int64_t>((int64_t)align_up((size_t)items, kWavesPerBlock),
+                                         (int64_t)fp.left_occ[i] * n_cu * kWavesPerBlock);
+  return std::min(want, fill_slots / kWavesPerBlock * kWavesPerBlock);
+}
+// and of the short-read ones together
+static int64_t left_short_waves(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t fill_slots) {
+  int64_t waves = 0;
+  for (int i = 0; i < fp.n_left; ++i)
+    if (!fp.left_long_reads[i]) waves = std::max(waves, left_waves(fp, i, n_cu, n_pairs, fill_slots));
+  return waves;
+}
+
+void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_t fill_slots, uint32_t* rerun,
+                  uint32_t* small) {
+  P->lcount = small + small::kLcount;
+  P->left_waves = (int32_t)left_short_waves(fp, n_cu, P->n_pairs, fill_slots);
+  P->pr_chunk = scan_chunk(n_cu, P->n_pairs);
+  const Params& S = fp.prune_shape;
+  P->presorted = rerun;
+  P->rcount = small + small::kRcount;
+  P->nbcount = small + small::kNbcount;
+  P->wbcount = small + small::kWbcount;
+  P->pqstart = small + small::kPqstart;
+  P->pr_slot_bytes = S.pr_slot_bytes;
+  P->pr_rec_bytes = S.pr_rec_bytes;
+  P->pr_slots = (int32_t)slots;
+  P->pr_scan_words = S.pr_scan_words;
+  P->pr_band_words = S.pr_band_words;
+  P->pr_win_words = S.pr_win_words;
+  P->pr_read_words = S.pr_read_words;
+  P->pr_part_words = S.pr_part_words;
+  P->pr_rows = S.pr_rows;
+  P->pr_group_words = S.pr_group_words;
+  P->pr_raw_off = S.pr_raw_off;
+  P->pr_raw_words = S.pr_raw_words;
+  P->pr_cost2 = S.pr_cost2;
+  P->pr_cost2_local = S.pr_cost2_local;
+  P->pr_leave2 = S.pr_leave2;
+  P->pr_leave2_local = S.pr_leave2_local;
+  P->pr_move2_del = S.pr_move2_del;
+  P->pr_move2_ins = S.pr_move2_ins;
+}
+
+void launch_sequence(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t slots, int64_t pr_slots,
+                     std::vector<Launch>* seq) {
+  const KernelTable& K = kernels();
+  if (n_pairs <= kFrontPairs) {
+    seq->push_back({K.front, 1, 256, 0, false});
+  } else {
+    const unsigned blocks = (unsigned)((n_pairs + kPlanPairsPerBlock - 1) / kPlanPairsPerBlock);
+    seq->push_back({K.zero, 1, 256, 0, false});
+    seq->push_back({K.plan, blocks, kPlanThreads, 0, false});
+    seq->push_back({K.scan, 1, 256, 0, false});
+    seq->push_back({K.scatter, blocks, kPlanThreads, 0, false});
+  }
+  if (pr_slots > 0) {
+    // an item per wave, at most one partial item per class and mode
+    const int64_t items = n_pairs / kPruneItem + kNumModes * kNumClasses;
+    const int64_t per_block = fp.prune_threads / 64;
+    const int64_t per_scan = fp.scan_threads / 64 * scan_chunk(n_cu, n_pairs);
+    const int64_t blocks = (std::min(items, n_pairs) + per_scan - 1) / per_scan;
+    seq->push_back({fp.scan_fn, (unsigned)blocks, (unsigned)fp.scan_threads, fp.scan_shmem, true});
+    for (int i = 0; i < fp.n_prune; ++i) {
+      const int64_t bands = std::min<int64_t>((int64_t)fp.prune_occ[i] * n_cu, pr_slots / per_block);
+      seq->push_back({fp.prune[i], (unsigned)bands, (unsigned)fp.prune_threads, fp.prune_shmem, true});
+    }
+    seq->push_back({K.rescan, 1, 256, 0, true});
+  }
+  bool lw_all = false;
+  if (pr_slots > 0) {
+    // (can the short reads' launches take whatever is left?)
+    const int64_t lw = left_short_waves(fp, n_cu, n_pairs, slots);
+    lw_all = 4 * lw >= n_pairs / fp.left_pairs + 2 * kNumClasses;
+    for (int i = 0; i < fp.n_left; ++i) {
+      const int64_t waves = left_waves(fp, i, n_cu, n_pairs, slots);
+      seq->push_back({fp.left[i], (unsigned)(waves / kWavesPerBlock), 256, kFillShmem, true});
+    }
+  }
+  for (int i = 0; i < fp.n; ++i) {
+    if (lw_all && fp.spare[i]) continue;
+    // each fill kernel gets the blocks it keeps resident (its waves index
+    // the first slots of the scratch)
+    const int64_t blocks = std::min<int64_t>((int64_t)fp.occ[i] * n_cu, slots / kWavesPerBlock);
+    if (fp.single[i]) seq->push_back({fp.fn[i], 1, 256, 0, true});
+    else seq->push_back({fp.fn[i], (unsigned)std::max<int64_t>(blocks, 1), 256, kFillShmem, true});
+  }
 }
 
 mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch_t* b, const mica_scoring_t* s,
@@ -307,7 +510,7 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
   const KernelTable& K = kernels();
   FillPlan& fp = *out;
   fp.n = 0;
-  for (int i = 0; i < kMaxFills; ++i) fp.single[i] = false;
+  for (int i = 0; i < kMaxFills; ++i) fp.single[i] = fp.spare[i] = false;
   fp.occ_max = 1;
   const int max_m = b->max_read_len, max_n = b->max_win_len;
   const int d = (flags & (MICA_OUT_CIGAR | MICA_OUT_START)) ? 1 : 0;
@@ -321,6 +524,11 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
   const bool may_sat = !forced && ((any_ext && b->max_ext_h0 == 0) ||
                                    !int16_always_safe(max_m, max_n, *s, any_local, any_sg, any_ext, b->max_ext_h0));
   const bool plain = flags & MICA_PLAIN_LAUNCH;
+  mica_status_t ps = plan_prune(device, class_of_m, b, *s, flags, d, any_mode, &fp);
+  if (ps != MICA_OK) return ps;
+  // the band kernels leave pairs to a mode's fills only without a traceback
+  // and for extensions; the saturating kinds they don't touch
+  auto filled = [&](int kind, int md) { return fp.n_prune == 0 || !d || md == 2 || !prune_kind(kind); };
   bool cls_used[kNumClasses] = {};
   for (int m = std::max(1, b->min_read_len); m <= max_m; ++m) cls_used[class_of_m[m]] = true;
   // a batch of one persistent class gains nothing from the persistent
@@ -337,13 +545,15 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
     // persistent parts in queue order: per mode, long reads first
     for (int md = 0; md < kNumModes; ++md) {
       if (!any_mode[md]) continue;
+      if (!filled(kK16, md)) continue;
       for (int part : {1, 0})
         if (part_used[part]) fp.fn[fp.n++] = K.persistent[d][md][part];
     }
   }
+  const bool any_persistent = fp.n > 0;
   // plain launches: every bucket in plain mode, else the buckets the
   // persistent kernels do not serve
-  auto plain_buckets = [&](const KernelFn* table) {
+  auto plain_buckets = [&](const KernelFn* table, bool side) {
     for (int kind = 0; kind < kNumKinds; ++kind) {
       if (forced != (kind == kK32)) continue;
       if (kind == kK16Sat && !may_sat) continue;
@@ -353,27 +563,37 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
           if (!any_mode[md]) continue;
           const int bk = bucket_id(kind, cls, md);
           if (persist && persistent_bucket(bk)) continue;
+          if (!side && !filled(kind, md)) continue;
+          fp.spare[fp.n] = side && !filled(kind, md) && !left_long(cls);
+          if (side && !filled(kind, md) && left_long(cls)) continue;  // k_seed_left's
           fp.fn[fp.n++] = table[bk];
         }
       }
     }
   };
-  plain_buckets(K.bucket[d]);
+  plain_buckets(K.bucket[d], false);
   // the side lists of the banded fills (pairs whose band was too wide: the
   // full traceback; bands of 17-64 diagonals: the band refill), after every
   // banded fill: persistent kernels over the persistent buckets (one queue
   // per mode and class part) and one launch per other bucket
   if (d) {
     if (persist) {
-      fp.single[fp.n] = true;
-      fp.fn[fp.n++] = K.sidescan;
+      // (without a fill of these buckets the scan after the band kernels has
+      // done it)
+      if (any_persistent) {
+        fp.single[fp.n] = true;
+        fp.fn[fp.n++] = K.sidescan;
+      }
       for (int md = 0; md < kNumModes; ++md) {
         if (!any_mode[md]) continue;
-        for (int part : {1, 0})
-          if (part_used[part]) fp.fn[fp.n++] = K.side_persistent[md][part];
+        for (int part : {1, 0}) {
+          if (!part_used[part]) continue;
+          fp.spare[fp.n] = !filled(kK16, md);
+          fp.fn[fp.n++] = K.side_persistent[md][part];
+        }
       }
     }
-    plain_buckets(K.side);
+    plain_buckets(K.side, true);
   }
   if (may_sat) fp.fn[fp.n++] = K.rerun[d];
   for (int i = 0; i < fp.n; ++i) {
@@ -381,10 +601,11 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
       fp.occ[i] = 1;
       continue;
     }
-    mica_status_t st = kernel_occupancy(device, fp.fn[i], &fp.occ[i]);
+    mica_status_t st = kernel_occupancy(device, fp.fn[i], 256, kFillShmem, &fp.occ[i]);
     if (st != MICA_OK) return st;
     fp.occ_max = std::max(fp.occ_max, fp.occ[i]);
   }
+  for (int i = 0; fp.n_prune && i < fp.n_left; ++i) fp.occ_max = std::max(fp.occ_max, fp.left_occ[i]);
   return MICA_OK;
 }
 
@@ -559,7 +780,11 @@ mica_status_t mica_dp_align_batch(mica_ctx_t c, const mica_batch_t* b, const mic
   if ((size_t)slots * sh.slot_bytes > c->ws_cap && slots > kWavesPerBlock)
     slots = (int64_t)(c->ws_cap / sh.slot_bytes) / kWavesPerBlock * kWavesPerBlock;
   if (slots < kWavesPerBlock) return fail(MICA_ERR_OUT_OF_MEMORY, "workspace too small for one block");
-  st = ensure_scratch(c, (size_t)slots * sh.slot_bytes);
+  // the band kernels run before the fills, in the same memory
+  const int64_t pr_want = prune_slots(fp, c->n_cu, b->n_pairs, c->ws_cap);
+  const size_t scratch_bytes =
+      std::max((size_t)slots * sh.slot_bytes, (size_t)pr_want * (size_t)fp.prune_shape.pr_slot_bytes);
+  st = ensure_scratch(c, scratch_bytes);
   if (st != MICA_OK) return st;
 
   // parameter block (pinned ring slot, copied on the stream)
@@ -594,25 +819,14 @@ mica_status_t mica_dp_align_batch(mica_ctx_t c, const mica_batch_t* b, const mic
   P.stage_stride = sh.stage_stride;
   P.n_slots = (int32_t)slots;
   for (int i = 0; i < kQueueParts; ++i) P.persist_q[i] = c->persist_q[i];
+  if (pr_want > 0) prune_params(&P, fp, c->n_cu, pr_want, slots, P.rerun, c->d_small);
   Params* dp = c->d_params + rp;
   HIP_TRY(hipMemcpyAsync(dp, &P, sizeof(Params), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipEventRecord(c->ev[rp], stream));
   c->ev_used[rp] = true;
 
-  const KernelTable& K = kernels();
-  const unsigned pblocks = (unsigned)((b->n_pairs + kPlanPairsPerBlock - 1) / kPlanPairsPerBlock);
   std::vector<Launch> seq;
-  seq.push_back({K.zero, 1, 256, 0, false});
-  seq.push_back({K.plan, pblocks, kPlanThreads, 0, false});
-  seq.push_back({K.scan, 1, 256, 0, false});
-  seq.push_back({K.scatter, pblocks, kPlanThreads, 0, false});
-  for (int i = 0; i < fp.n; ++i) {
-    // each fill kernel gets the blocks it keeps resident (its waves index
-    // the first slots of the scratch)
-    const int64_t blocks = std::min<int64_t>((int64_t)fp.occ[i] * c->n_cu, slots / kWavesPerBlock);
-    if (fp.single[i]) seq.push_back({fp.fn[i], 1, 256, 0, true});
-    else seq.push_back({fp.fn[i], (unsigned)std::max<int64_t>(blocks, 1), 256, kFillShmem, true});
-  }
+  launch_sequence(fp, c->n_cu, b->n_pairs, slots, pr_want, &seq);
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (c->timing) {
     HIP_TRY(take_event(c, &t0));
@@ -623,7 +837,7 @@ mica_status_t mica_dp_align_batch(mica_ctx_t c, const mica_batch_t* b, const mic
   if (c->timing) c->ev_pending.emplace_back(t0, t1);
   c->last_pairs = b->n_pairs;
   c->last_slots = (int)slots;
-  c->last_scratch = (size_t)slots * sh.slot_bytes;
+  c->last_scratch = scratch_bytes;
   return MICA_OK;
 }
 
@@ -666,7 +880,8 @@ mica_status_t mica_ctx_last_stats(mica_ctx_t c, void* stream, mica_batch_stats_t
   HIP_TRY(hipMemcpy(fbc, small_fbcount(c), sizeof(fbc), hipMemcpyDeviceToHost));
   out->n_fallback = 0;
   for (int b = 0; b < kNumBuckets; ++b) out->n_fallback += fbc[b];
-  out->n_deferred = 0;
+  out->n_fallback += (int64_t)ctr[kCtrPruneWide] - (int64_t)ctr[kCtrPruneLeft];
+  out->n_deferred = ctr[kCtrPruneMid];
   for (size_t list : {small::kDbcount, small::kDbwide}) {
     HIP_TRY(hipMemcpy(fbc, c->d_small + list, sizeof(fbc), hipMemcpyDeviceToHost));
     for (int b = 0; b < kNumBuckets; ++b) out->n_deferred += fbc[b];

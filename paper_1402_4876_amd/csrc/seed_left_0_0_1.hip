@@ -1,0 +1,7 @@
+// Full traceback of the pairs the seeded band kernels leave: packed 16-bit scores,
+// semi-global, reads of more than 256 bases.
+#include "seed.h"
+
+namespace mica {
+void reg_seed_left_0_0_1(KernelTable& t) { t.seed_left[0][0][1] = &k_seed_left<V16, 0, true>; }
+}  // namespace mica

@@ -1,0 +1,7 @@
+// Full traceback of the pairs the seeded band kernels leave: 32-bit scores,
+// local, reads of up to 256 bases.
+#include "seed.h"
+
+namespace mica {
+void reg_seed_left_1_1_0(KernelTable& t) { t.seed_left[1][1][0] = &k_seed_left<V32, 1, false>; }
+}  // namespace mica
