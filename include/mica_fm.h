@@ -55,8 +55,9 @@ typedef struct mica_fm *mica_fm_t;
 /* Build the FM index of a reference given as host 2-bit words (ref_len
  * bases, base k of a word at bits 2(k mod 16)) and upload it to HIP device
  * hip_device: occurrence blocks (64 B per 192 BWT symbols: four 32-bit counts
- * and twelve words of 2-bit symbols), the full 32-bit suffix array and a
- * padded copy of the reference.  The build runs on the calling host thread;
+ * and twelve words of 2-bit symbols), the full 32-bit suffix array, a
+ * padded copy of the reference and a table of the intervals of all strings
+ * of up to 12 bases (at most twice the reference's length in bytes).  The build runs on the calling host thread;
  * the device memory stays allocated until mica_fm_destroy. */
 mica_status_t mica_fm_create(int hip_device, const uint32_t *host_ref2b, uint64_t ref_len, mica_fm_t *out);
 

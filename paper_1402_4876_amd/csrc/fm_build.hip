@@ -145,6 +145,7 @@ struct mica_fm {
   void* d_occ = nullptr;
   void* d_sa = nullptr;
   void* d_ref = nullptr;
+  void* d_kmer = nullptr;
   uint64_t bytes = 0;
   double build_s = 0;
 };
@@ -168,6 +169,7 @@ mica_status_t release(mica_fm* f) {
   if (f->d_occ) (void)hipFree(f->d_occ);
   if (f->d_sa) (void)hipFree(f->d_sa);
   if (f->d_ref) (void)hipFree(f->d_ref);
+  if (f->d_kmer) (void)hipFree(f->d_kmer);
   delete f;
   return MICA_OK;
 }
@@ -226,6 +228,23 @@ mica_status_t build(mica_fm* f, const uint32_t* host_ref2b, uint64_t n) {
   f->ix.ref2b = (const uint32_t*)f->d_ref;
   f->ix.ref_words = ref_words;
   f->bytes = occ.size() * 4 + rows * 4 + ref_words * 4;
+  // the interval table (a search without one steps through every base)
+  f->ix.kmer = nullptr;
+  f->ix.kmer_k = 0;
+  const int k = fm_kmer_bases(n);
+  void* tmp = nullptr;
+  if (k > 0 && hipMalloc(&f->d_kmer, (size_t)8 << (2 * k)) == hipSuccess) {
+    hipError_t e = hipMalloc(&tmp, (size_t)8 << (2 * (k > 1 ? k - 1 : 1)));
+    if (e == hipSuccess) e = fm_build_kmers(f->ix, k, (uint32_t*)f->d_kmer, (uint32_t*)tmp);
+    if (tmp) (void)hipFree(tmp);
+    HIP_TRY(e);
+    f->ix.kmer = (const uint32_t*)f->d_kmer;
+    f->ix.kmer_k = k;
+    f->bytes += (uint64_t)8 << (2 * k);
+  } else if (k > 0) {
+    f->d_kmer = nullptr;
+    (void)hipGetLastError();
+  }
   return MICA_OK;
 }
 

@@ -1,5 +1,7 @@
 // FM index layout shared by the index build (host) and the search kernel.
 #pragma once
+#include <hip/hip_runtime.h>
+
 #include <cstdint>
 
 struct mica_fm;
@@ -17,11 +19,25 @@ struct FmIndex {
   const uint32_t* ref2b;  // reference, 2-bit words, two words of zero padding
   uint64_t n;           // reference length
   uint64_t ref_words;
+  const uint32_t* kmer;  // {first row, row past the last} of every string of kmer_k bases (base t
+  int kmer_k;            // of the string at bits 2t of its number); 0: no table
   uint32_t C[4];        // first row of the suffixes starting with each base
   uint32_t dollar;      // BWT row holding the sentinel (stored as code 0, not counted)
   int device;           // HIP device holding the index
 };
 
 const FmIndex* fm_index_of(const mica_fm* f);
+
+// Bases of the table's strings: as many as keep it within twice the
+// reference's length in bytes, 12 at most (134 MB).
+constexpr int kFmMaxKmer = 12;
+inline int fm_kmer_bases(uint64_t n) {
+  int k = 0;
+  while (k < kFmMaxKmer && (8ull << (2 * (k + 1))) <= 2 * n) ++k;
+  return k;
+}
+// Fills table (4^k entries) from the index on its device, level by level (tmp:
+// another 4^k entries); waits for the result.
+hipError_t fm_build_kmers(const FmIndex& ix, int k, uint32_t* table, uint32_t* tmp);
 
 }  // namespace mica
