@@ -71,7 +71,7 @@ struct FillPlan {
   KernelFn fn[kMaxFills];
   int occ[kMaxFills];
   bool single[kMaxFills];  // one block of 256 threads without dynamic LDS (a scan between fills)
-  // side lists whose pairs k_seed_left takes whenever it has the waves for all
+  // launches whose pairs k_seed_left takes whenever it has the waves for all
   bool spare[kMaxFills];
   int n = 0;
   int occ_max = 1;
@@ -86,9 +86,9 @@ struct FillPlan {
   int n_prune = 0;
   int prune_threads = 256;
   size_t prune_shmem = 0;
-  KernelFn left[4];
-  int left_occ[4];
-  bool left_long_reads[4];
+  KernelFn left[2 * kNumModes];
+  int left_occ[2 * kNumModes];
+  bool left_long_reads[2 * kNumModes];
   int n_left = 0;
   int left_pairs = 2;  // pairs per item
   Params prune_shape;       // the pr_ members only

@@ -228,6 +228,7 @@ struct Params {
   uint32_t* presorted;         // [n_pairs] the planner's order; what they leave goes to `sorted`
   uint32_t* rcount;            // [kNumBuckets] pairs left per bucket
   uint32_t* lcount;            // [kNumBuckets] pairs left to k_seed_left
+  int32_t left_full_;          // pairs left go to the full traceback without a fill (see left_full)
   int32_t left_waves;          // waves of its short-read launches (0: there are none)
   uint32_t* nbcount;           // [kNumBuckets] pairs on the band lists, one strip
   uint32_t* wbcount;           // [kNumBuckets] and more
@@ -245,6 +246,13 @@ struct Params {
   uint32_t persist_q[kQueueParts];  // queue positions [persist_q[q], persist_q[q+1]) of queue part q
 };
 
+// Where many pairs are left of a batch with a traceback: to the full traceback
+// at once, since most of them (unrelated, or far from their diagonal) would end
+// there after a score-only fill too.  Not extensions and reads of up to 100
+// bases, whose band is narrow more often than not.
+__host__ __device__ inline bool left_full(const Params* p, int mode) { return p->left_full_ && mode != 2; }
+constexpr int kLeftFullRead = 100;
+
 }  // namespace mica
 
 namespace mica {
@@ -260,7 +268,7 @@ struct KernelTable {
   KernelFn sidescan;
   KernelFn seed_scan[2][2];             // [with traceback][32-bit]
   KernelFn seed_band[2][2][kNumModes];  // [with traceback][32-bit][mode]
-  KernelFn seed_left[2][2][2];          // [32-bit][mode][long reads]
+  KernelFn seed_left[2][kNumModes][2];  // [32-bit][mode][long reads]
   KernelFn rescan;                      // after them
   KernelFn front;                       // zero, plan, scan and scatter of a small batch
   KernelFn rerun[2];

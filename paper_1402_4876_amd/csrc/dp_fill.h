@@ -238,11 +238,12 @@ enum Traceback : int { kTbNone = 0, kTbBand = 1, kTbFull = 2, kTbDefer = 3, kTbP
 
 // One wave-sized work item: G = 64/P groups, each aligning kPairs pairs.
 // pend: the count of the wave's pending list (banded fills of 16-lane
-// classes; unused otherwise).
+// classes; unused otherwise).  from_left: pairs the seeded band kernels left.
 template <class V, int P, int R, int MODE, int TB, bool SAT>
 __device__ __forceinline__ void process_item(const Params* __restrict__ prm,
                                           const uint32_t* __restrict__ pairs, int npairs,
-                                          uint32_t* lds, uint8_t* slot, int bucket, int* pend = nullptr) {
+                                          uint32_t* lds, uint8_t* slot, int bucket, int* pend = nullptr,
+                                          bool from_left = false) {
   typedef typename V::T T;
   constexpr bool DIR = (TB == kTbFull);
   constexpr int NP = V::kPairs;
@@ -733,7 +734,8 @@ __device__ __forceinline__ void process_item(const Params* __restrict__ prm,
   const int h = k / X;
   const int x = k - h * X;
   // (pairs the seeded band kernels left come here without a banded fill)
-  const bool left = TB == kTbFull && MODE != 2 && !SAT && bucket >= 0 && prm->presorted != nullptr;
+  const bool left = TB == kTbFull && !SAT && bucket >= 0 &&
+                    (from_left || (prm->presorted != nullptr && left_full(prm, MODE)));
   BandCount width{0, 0};
   if (g * NP + h < npairs) {
     // the pair's parameters are read again here rather than kept in
@@ -760,7 +762,10 @@ __device__ __forceinline__ void process_item(const Params* __restrict__ prm,
         G(prm->score)[p_] = score;
         G(prm->read_end)[p_] = ie;
         G(prm->ref_end)[p_] = je;
-        if (left) band_count<V, MODE>(prm, m_, n_, 0, score, ie, je, &width);
+        if (left) {
+          const int h0_ = EXT ? (prm->ext_h0 ? G(prm->ext_h0)[p_] : prm->ext_default_h0) : 0;
+          band_count<V, MODE>(prm, m_, n_, h0_, score, ie, je, &width);
+        }
       }
       uint32_t st = 0;
       if constexpr (DIR) {

@@ -265,33 +265,32 @@ __global__ __launch_bounds__(kScanThreads) void k_sidescan(const Params* __restr
   sidescan_tables(prm, sh);
 }
 
-// After the band kernels: bucket sizes and queue of the pairs they left, to
-// the fills or to the full traceback.
+// After the band kernels: the pairs they left, to k_seed_left, to the full
+// traceback of the side lists or to the fills.
 __global__ __launch_bounds__(kScanThreads) void k_rescan(const Params* __restrict__ prm) {
   __shared__ uint32_t sh[kScanThreads];
   const int q = threadIdx.x;
-  // (see left_list of the band kernels)
   const bool traced = (prm->flags & (kOutStart | kOutCigar)) != 0;
-  auto full = [&](int b) { return traced && prune_kind(bucket_kind(b)) && bucket_mode(b) != 2; };
-  // few enough for the kernel that takes them a wave each?
+  auto seeded = [&](int b) { return traced && prune_kind(bucket_kind(b)); };
+  // short reads: few enough for the kernel that takes them a wave an item?
   uint32_t waves = 0, all_waves;
-  if (q < kNumBuckets && full(q) && !left_long(bucket_class(q))) {
+  if (q < kNumBuckets && seeded(q) && !left_long(bucket_class(q))) {
     const uint32_t per = bucket_kind(q) == kK32 ? 1u : 2u;
     waves = (prm->rcount[q] + per - 1) / per;
   }
   (void)block_exclusive_scan(waves, sh, &all_waves);
   const bool few = all_waves <= 4u * (uint32_t)prm->left_waves;
+  auto by_wave = [&](int b) { return seeded(b) && (few || left_long(bucket_class(b))); };
+  auto full = [&](int b) { return seeded(b) && !by_wave(b) && left_full(prm, bucket_mode(b)); };
   uint32_t items = 0, left = 0;
   if (q < kNumBuckets) {
     const int bq = (int)prm->qorder[q];
     const uint32_t ppi = (uint32_t)pairs_per_item(bucket_kind(bq), bucket_class(bq));
-    items = full(bq) ? 0u : (prm->rcount[bq] + ppi - 1) / ppi;
+    items = by_wave(bq) || full(bq) ? 0u : (prm->rcount[bq] + ppi - 1) / ppi;
     left = full(q) ? prm->rcount[q] : 0u;
-    prm->bcount[q] = full(q) ? 0u : prm->rcount[q];
-    const bool mine = full(q) && (few || left_long(bucket_class(q)));
-    prm->lcount[q] = mine ? left : 0u;
-    if (full(q)) prm->fbcount[q] = mine ? 0u : left;
-    if (mine) left = 0;  // (not among fbcount's)
+    prm->lcount[q] = by_wave(q) ? prm->rcount[q] : 0u;
+    prm->bcount[q] = by_wave(q) || full(q) ? 0u : prm->rcount[q];
+    prm->fbcount[q] = left;
   }
   uint32_t n_items, n_left;
   const uint32_t qs = block_exclusive_scan(items, sh, &n_items);
@@ -410,7 +409,9 @@ MICA_PERSIST_SIDE_ALL(MICA_PERSIST_SIDE_DECL)
 #define MICA_SEED_DECL(tb, wide, mode) void reg_seed_##tb##_##wide##_##mode(KernelTable& t);
 MICA_SEED_ALL(MICA_SEED_DECL)
 
-#define MICA_LEFT_ALL(X) X(0, 0, 0) X(0, 0, 1) X(0, 1, 0) X(0, 1, 1) X(1, 0, 0) X(1, 0, 1) X(1, 1, 0) X(1, 1, 1)
+#define MICA_LEFT_ALL(X) \
+  X(0, 0, 0) X(0, 0, 1) X(0, 1, 0) X(0, 1, 1) X(0, 2, 0) X(0, 2, 1) \
+  X(1, 0, 0) X(1, 0, 1) X(1, 1, 0) X(1, 1, 1) X(1, 2, 0) X(1, 2, 1)
 #define MICA_LEFT_DECL(wide, mode, lng) void reg_seed_left_##wide##_##mode##_##lng(KernelTable& t);
 #define MICA_LEFT_CALL(wide, mode, lng) reg_seed_left_##wide##_##mode##_##lng(*this);
 MICA_LEFT_ALL(MICA_LEFT_DECL)

@@ -375,9 +375,10 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
     ++n_prune;
   }
   fp->n_prune = n_prune;
+  S.left_full_ = traced && m > kLeftFullRead ? 1 : 0;
   fp->n_left = 0;
   fp->left_pairs = wide ? 1 : 2;
-  for (int md = 0; md < 2 && traced; ++md)
+  for (int md = 0; md < kNumModes && traced; ++md)
     for (int lng = 0; lng < 2; ++lng) {
       bool used = false;
       for (int r = std::max(1, b->min_read_len); r <= m; ++r) used |= (left_long(class_of_m[r]) ? 1 : 0) == lng;
@@ -440,6 +441,7 @@ void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_
   P->nbcount = small + small::kNbcount;
   P->wbcount = small + small::kWbcount;
   P->pqstart = small + small::kPqstart;
+  P->left_full_ = S.left_full_;
   P->pr_slot_bytes = S.pr_slot_bytes;
   P->pr_rec_bytes = S.pr_rec_bytes;
   P->pr_slots = (int32_t)slots;
@@ -489,7 +491,7 @@ void launch_sequence(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t slot
   if (pr_slots > 0) {
     // (can the short reads' launches take whatever is left?)
     const int64_t lw = left_short_waves(fp, n_cu, n_pairs, slots);
-    lw_all = 4 * lw >= n_pairs / fp.left_pairs + 2 * kNumClasses;
+    lw_all = 4 * lw >= n_pairs / fp.left_pairs + kNumModes * kNumClasses;
     for (int i = 0; i < fp.n_left; ++i) {
       const int64_t waves = left_waves(fp, i, n_cu, n_pairs, slots);
       seq->push_back({fp.left[i], (unsigned)(waves / kWavesPerBlock), 256, kFillShmem, true});
@@ -526,9 +528,11 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
   const bool plain = flags & MICA_PLAIN_LAUNCH;
   mica_status_t ps = plan_prune(device, class_of_m, b, *s, flags, d, any_mode, &fp);
   if (ps != MICA_OK) return ps;
-  // the band kernels leave pairs to a mode's fills only without a traceback
-  // and for extensions; the saturating kinds they don't touch
-  auto filled = [&](int kind, int md) { return fp.n_prune == 0 || !d || md == 2 || !prune_kind(kind); };
+  // what the band kernels leave of their kinds with a traceback: reads of the
+  // long classes to k_seed_left, others there (spare) or, where they are many,
+  // to the side lists or the fills
+  auto seeded = [&](int kind) { return fp.n_prune > 0 && d && prune_kind(kind); };
+  auto filled = [&](int kind, int md) { return !seeded(kind) || !left_full(&fp.prune_shape, md); };
   bool cls_used[kNumClasses] = {};
   for (int m = std::max(1, b->min_read_len); m <= max_m; ++m) cls_used[class_of_m[m]] = true;
   // a batch of one persistent class gains nothing from the persistent
@@ -546,8 +550,11 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
     for (int md = 0; md < kNumModes; ++md) {
       if (!any_mode[md]) continue;
       if (!filled(kK16, md)) continue;
-      for (int part : {1, 0})
-        if (part_used[part]) fp.fn[fp.n++] = K.persistent[d][md][part];
+      for (int part : {1, 0}) {
+        if (!part_used[part]) continue;
+        fp.spare[fp.n] = seeded(kK16);
+        fp.fn[fp.n++] = K.persistent[d][md][part];
+      }
     }
   }
   const bool any_persistent = fp.n > 0;
@@ -563,9 +570,9 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
           if (!any_mode[md]) continue;
           const int bk = bucket_id(kind, cls, md);
           if (persist && persistent_bucket(bk)) continue;
+          if (seeded(kind) && left_long(cls)) continue;
           if (!side && !filled(kind, md)) continue;
-          fp.spare[fp.n] = side && !filled(kind, md) && !left_long(cls);
-          if (side && !filled(kind, md) && left_long(cls)) continue;  // k_seed_left's
+          fp.spare[fp.n] = seeded(kind);
           fp.fn[fp.n++] = table[bk];
         }
       }
@@ -582,13 +589,14 @@ mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch
       // done it)
       if (any_persistent) {
         fp.single[fp.n] = true;
+        fp.spare[fp.n] = seeded(kK16);
         fp.fn[fp.n++] = K.sidescan;
       }
       for (int md = 0; md < kNumModes; ++md) {
         if (!any_mode[md]) continue;
         for (int part : {1, 0}) {
           if (!part_used[part]) continue;
-          fp.spare[fp.n] = !filled(kK16, md);
+          fp.spare[fp.n] = seeded(kK16);
           fp.fn[fp.n++] = K.side_persistent[md][part];
         }
       }

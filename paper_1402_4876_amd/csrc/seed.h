@@ -188,21 +188,18 @@ __device__ __forceinline__ bool band_fits(const Params* __restrict__ prm, int m,
   return top + off <= 32767 && off <= 32767 && low <= 32767;
 }
 
-// Where the pairs left go: with a traceback straight to the full one, since
-// most of them (unrelated, or far from their diagonal) would end there after a
-// score-only fill too; extensions, whose band follows from a short early end
-// more often than not, and pairs without a traceback to the fills.
+// The list of the pairs left and the list of bands, each in a bucket's range:
+// the two lists the fills use later, the left pairs in the one they are read
+// from (left_full of the planner).  Bands of one strip go from the start of
+// the range up, wider ones from its end down; their bands and cores lie in
+// arrays by pair that are free between the planner and the fills.
 template <int MODE, bool TRACE>
 __device__ __forceinline__ MICA_GLOBAL uint32_t* left_list(const Params* __restrict__ prm) {
-  return G(TRACE && MODE != 2 ? prm->fbsorted : prm->sorted);
+  return G(TRACE && left_full(prm, MODE) ? prm->fbsorted : prm->sorted);
 }
-// The list of bands: one strip from the start of a bucket's range up, more from
-// its end down.  (Whichever of the two lists the left pairs don't use; the
-// bands and cores lie in arrays by pair that are free between the planner and
-// the fills.)
 template <int MODE, bool TRACE>
 __device__ __forceinline__ MICA_GLOBAL uint32_t* band_list(const Params* __restrict__ prm) {
-  return G(TRACE && MODE != 2 ? prm->sorted : prm->fbsorted);
+  return G(TRACE && left_full(prm, MODE) ? prm->sorted : prm->fbsorted);
 }
 // Adds the pairs of the lanes with `mine` to list li (0 left, 1 one strip, 2
 // more) of the wave's output.
@@ -556,9 +553,12 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
     } else {
       // the loss to expect: parts without an occurrence stand for
       // substitutions, two diagonals (or a tail full of mismatches) for a gap
-      int loss = (sa - sb) * missed;
+      // (u of T parts hit at random hold some u + u u / 2 T of them)
+      // (where a band that fails costs more than it may save: without a traceback)
+      auto subs = [&](int u) -> int { return (sa - sb) * (TRACE ? u : u + u * u / (2 * T)); };
+      int loss = subs(missed);
       if (core.span > 0) {
-        loss = so + (se + sa) * (core.span < 4 ? core.span : 4) + (sa - sb) * (missed > 1 ? missed - 1 : 0);
+        loss = so + (se + sa) * (core.span < 4 ? core.span : 4) + subs(missed > 1 ? missed - 1 : 0);
       } else if (!one || mism > missed + 1) {
         loss += so + 2 * se;
       }
@@ -976,7 +976,7 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
 // The full traceback of the pairs left, by whole waves of as few rows a lane
 // as the item's reads need: those of up to 256 bases (LONG false) where they
 // are few, at most four items per resident wave, so that the time of one item,
-// which is the launch's, is short (150 x 400: 3 rows a lane in place of 10, and
+// which is then the launch's, is short (150 x 400: 3 rows a lane in place of 10, and
 // of the 4 of the side lists' kernels, which also take a launch per mode and
 // length range); longer ones always (their class has 16 rows a lane whatever
 // the read).
@@ -984,14 +984,14 @@ template <class V, int MODE, bool LONG>
 __device__ __forceinline__ void left_item(const Params* __restrict__ prm, const uint32_t* pairs, int np, int m,
                                           uint32_t* lds, uint8_t* slot, int bucket) {
   if constexpr (LONG) {
-    if (m <= 384) process_item<V, 64, 6, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
-    else if (m <= 512) process_item<V, 64, 8, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
-    else if (m <= 768) process_item<V, 64, 12, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
-    else process_item<V, 64, 16, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
+    if (m <= 384) process_item<V, 64, 6, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
+    else if (m <= 512) process_item<V, 64, 8, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
+    else if (m <= 768) process_item<V, 64, 12, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
+    else process_item<V, 64, 16, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
   } else {
-    if (m <= 128) process_item<V, 64, 2, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
-    else if (m <= 192) process_item<V, 64, 3, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
-    else process_item<V, 64, 4, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket);
+    if (m <= 128) process_item<V, 64, 2, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
+    else if (m <= 192) process_item<V, 64, 3, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
+    else process_item<V, 64, 4, MODE, kTbFull, false>(prm, pairs, np, lds, slot, bucket, nullptr, true);
   }
 }
 template <class V, int MODE, bool LONG>
@@ -1024,7 +1024,7 @@ __global__ __launch_bounds__(256, LONG ? 2 : 4) void k_seed_left(const Params* _
     const uint32_t have = (uint32_t)__builtin_amdgcn_readlane((int)pairs, k) - first;
     const int np = have < (uint32_t)PPI ? (int)have : PPI;
     const int bucket = bucket_id(KIND, prune_class(k), MODE);
-    const uint32_t* list = prm->fbsorted + G(prm->bstart)[bucket] + first;
+    const uint32_t* list = (const uint32_t*)left_list<MODE, true>(prm) + G(prm->bstart)[bucket] + first;
     int m = 0;
     for (int s = 0; s < np; ++s) {
       const int ms = G(prm->read_len)[G(list)[s]];

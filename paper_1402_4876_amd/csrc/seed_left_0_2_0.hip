@@ -1,0 +1,7 @@
+// Full traceback of the pairs the seeded band kernels leave: packed 16-bit scores,
+// seed extension, reads of up to 256 bases.
+#include "seed.h"
+
+namespace mica {
+void reg_seed_left_0_2_0(KernelTable& t) { t.seed_left[0][2][0] = &k_seed_left<V16, 2, false>; }
+}  // namespace mica
