@@ -72,6 +72,8 @@ __device__ __forceinline__ uint32_t and_or(uint32_t p, uint32_t m, uint32_t a) {
 }
 constexpr int kDppShl1 = 0x101, kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;
 constexpr int kDppRor15 = 0x12F, kDppBcast15 = 0x15F;  // row_ror:15, row_newbcast:15
+// wave_shl:1, wave_shr:1; a row's last lane to the next row, lane 31 to rows 2 and 3
+constexpr int kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138, kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
 
 // Per band group (or per wave for the 64-lane classes): read selectors per
 // row, then the window codes.  Window entry e holds, for each pair, the code
@@ -267,11 +269,14 @@ struct BandFind {
   int top[2];
 };
 
-// The band DP of a wave's groups of 16 lanes, rows 1 to rows_u, in ns_u strips.
+// The band DP of a wave's groups of LG lanes, rows 1 to rows_u, in ns_u strips
+// (one where LG > 16: a band of up to LG diagonals in one pass of the lanes;
+// its insertions and deletions cross the 16-lane rows by wave shifts and row
+// broadcasts).
 // TRACE keeps the sign bits of every cell; FIND also keeps what tells the
 // result cell.  Rows up to mr_u may touch column 0 or lie left of it; rows
 // from tail_u on may be past the end of a pair (FIND).
-template <class V, int MODE, int NS, bool TRACE, bool FIND>
+template <class V, int MODE, int NS, bool TRACE, bool FIND, int LG = 16>
 __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, const int* dlo, const int* W,
                                             const int* d0, const int* h0, const bool* act, int rows_u, int ns_u,
                                             int mr_u, int tail_u, const uint32_t* gq, const uint16_t* gw,
@@ -282,7 +287,8 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
   constexpr bool EXT = (MODE == 2);
   constexpr bool TRACK = (MODE != 0);
   const int lane = threadIdx.x & 63;
-  const int l = lane & 15;
+  static_assert(LG == 16 || NS == 1, "one strip in a wide group");
+  const int l = lane & (LG - 1);
   const int ns64 = ns_u * 64;
   const int sa = prm->sa, sb = prm->sb, so = prm->so, se = prm->se;
   const int oe = so + se;
@@ -310,6 +316,8 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
   T Hd[NS], Ic[NS], msk[NS];
   uint32_t acc[NS];
   const uint16_t* gwl = gw + l;
+  const uint32_t inner = l == 0 ? 0u : ~0u;  // no deletion comes in from another group
+  (void)inner;
   // the score table's low half as a register operand of the lookup
   uint32_t tab_lo_v;
   asm("v_mov_b32 %0, %1" : "=v"(tab_lo_v) : "s"(tab_lo));
@@ -331,7 +339,9 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
       iv[h] = hv[h] - oe;
       neg[h] = j < 0;
       if constexpr (FIND) neg[h] = neg[h] && find->top[h] == 0;
-      mk[h] = act[h] && gl < W[h];
+      // (a wide group's first lane feeds no insertion: its neighbour below the
+      // band is another group's last)
+      mk[h] = act[h] && gl < W[h] && (LG == 16 || l != 0);
     }
     uint32_t nm = 0;
     if constexpr (NP == 2) {
@@ -410,7 +420,7 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
       // insertion from the next diagonal one row up
       T old = negv;
       if (s + 1 < NS && s + 1 < ns_u) old = MICA_DPP(negv, Ic[s + 1 < NS ? s + 1 : s], kDppRor15);
-      const T Iv = MICA_DPP(old, Ic[s], kDppShl1);
+      const T Iv = LG == 16 ? MICA_DPP(old, Ic[s], kDppShl1) : MICA_DPP(old, Ic[s], kDppWaveShl1);
       T Hp = V::vmax(x, Iv);
       if constexpr (LOCAL) Hp = V::vmax(Hp, floor_v);
       if constexpr (MASKED) {
@@ -443,8 +453,11 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
         g = umax(g, dpp_zero<kDppShr2>(g));
         g = umax(g, dpp_zero<kDppShr4>(g));
         g = umax(g, dpp_zero<kDppShr8>(g));
+        if constexpr (LG > 16) g = umax(g, (uint32_t)__builtin_amdgcn_update_dpp((int)g, (int)g, kDppRowBcast15, 0xA, 0xF, false));
+        if constexpr (LG > 32) g = umax(g, (uint32_t)__builtin_amdgcn_update_dpp((int)g, (int)g, kDppRowBcast31, 0xC, 0xF, false));
         if (s > 0) g = umax(g, (uint32_t)carry);
-        uint32_t excl = dpp_zero<kDppShr1>(g);
+        uint32_t excl = LG == 16 ? dpp_zero<kDppShr1>(g) : dpp_zero<kDppWaveShr1>(g);
+        if constexpr (LG == 32) excl &= inner;
         if (s > 0) excl = umax(excl, (uint32_t)carry);
         Dv = V::sub((T)(excl ^ kFlip), og);
         if (s + 1 < NS && s + 1 < ns_u) carry = (T)((uint32_t)V::sub((T)(dpp_zero<kDppBcast15>(g) ^ kFlip), e16) ^ kFlip);
@@ -454,8 +467,11 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
         g = V::vmax(g, MICA_DPP(negv, g, kDppShr2));
         g = V::vmax(g, MICA_DPP(negv, g, kDppShr4));
         g = V::vmax(g, MICA_DPP(negv, g, kDppShr8));
+        if constexpr (LG > 16) g = V::vmax(g, (T)__builtin_amdgcn_update_dpp((int)g, (int)g, kDppRowBcast15, 0xA, 0xF, false));
+        if constexpr (LG > 32) g = V::vmax(g, (T)__builtin_amdgcn_update_dpp((int)g, (int)g, kDppRowBcast31, 0xC, 0xF, false));
         if (s > 0) g = V::vmax(g, carry);
-        const T excl = MICA_DPP(carry, g, kDppShr1);
+        T excl = LG == 16 ? MICA_DPP(carry, g, kDppShr1) : MICA_DPP(carry, g, kDppWaveShr1);
+        if constexpr (LG == 32) excl = (T)bfi(inner, (uint32_t)excl, (uint32_t)negv);
         Dv = V::sub(excl, og);
         if (s + 1 < NS && s + 1 < ns_u) carry = V::sub(MICA_DPP(negv, g, kDppBcast15), e16);
       }
@@ -556,28 +572,29 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
 // state the eight groups of an item took up to 100 us to walk in turn, and
 // 10 us each alone.
 constexpr int kWalkStage = 16;
-template <class V, int MODE>
+template <class V, int MODE, int LG = 16>
 __device__ __forceinline__ void band_walk(const Params* __restrict__ prm, const MICA_GLOBAL uint32_t* rec,
                                           uint32_t* lst, MICA_GLOBAL uint32_t* stg, int ns64, int p, int m, int n,
                                           int ie, int je, int dlo, int W, int top = 0) {
   constexpr bool LOCAL = (MODE == 1);
   constexpr bool EXT = (MODE == 2);
-  constexpr int X = 16 / V::kPairs;
-  constexpr int C = 16;
+  constexpr int X = LG / V::kPairs;
+  constexpr int C = X <= 8 ? 16 : (X <= 32 ? 128 / X : 2);
   const int lane = threadIdx.x & 63;
-  const int bg = lane >> 4;
-  const int h = (lane & 15) / X;
-  const int x = (lane & 15) - h * X;
+  const int bg = lane / LG;
+  const int h = (lane & (LG - 1)) / X;
+  const int x = (lane & (LG - 1)) - h * X;
   const int lane0 = lane - x;
-  constexpr uint64_t xmask = (1ull << X) - 1;
-  const MICA_GLOBAL uint32_t* const mine = rec + bg * 16;
+  constexpr uint64_t xmask = X == 64 ? ~0ull : (1ull << (X == 64 ? 0 : X)) - 1;
+  const MICA_GLOBAL uint32_t* const mine = rec + bg * LG;
   auto in_band = [&](int i, int j) -> bool {
     const int gl = j - i - dlo;
     return i >= 1 && gl >= 0 && gl < W;
   };
   // the record word of row pair rp (0-based rows 2 rp, 2 rp + 1) on a diagonal
   auto word = [&](int rp, int gl) -> uint32_t {
-    return mine[(size_t)rp * (size_t)ns64 + (size_t)((gl >> 4) * 64 + (gl & 15))];
+    if constexpr (LG == 16) return mine[(size_t)rp * (size_t)ns64 + (size_t)((gl >> 4) * 64 + (gl & 15))];
+    else return mine[(size_t)rp * 64 + (size_t)gl];
   };
   int i = ie, j = je;
   int state = 0;  // 0: H, 1: D, 2: I

@@ -48,8 +48,9 @@ constexpr size_t kDbqstart = kDbwide + kNumBuckets;  // kNumBuckets + 1 entries
 constexpr size_t kRcount = kDbqstart + kNumBuckets + 8;
 constexpr size_t kLcount = kRcount + kNumBuckets;
 constexpr size_t kNbcount = kLcount + kNumBuckets;
-constexpr size_t kWbcount = kNbcount + kNumBuckets;
-constexpr size_t kPqstart = kWbcount + kNumBuckets;  // kPruneParts * (kNumClasses + 1) entries
+constexpr size_t kW32count = kNbcount + kNumBuckets;
+constexpr size_t kW64count = kW32count + kNumBuckets;
+constexpr size_t kPqstart = kW64count + kNumBuckets;  // kPruneParts * (kNumClasses + 1) entries
 constexpr size_t kWords = kPqstart + kPruneParts * (kNumClasses + 1) + 8;
 }  // namespace small
 
@@ -65,8 +66,8 @@ mica_status_t check_batch(const mica_batch_t* b, const mica_scoring_t* s, uint32
 // The fill launches of a batch, in launch order, and the resident blocks per
 // CU of each (its occupancy at the library's block shape).
 constexpr int kMaxFills = 4 * kNumModes + 2 * kNumBuckets + 2;
-// per-pair work lists of a batch: bucket_of | sorted | rerun | fbsorted | dbsorted
-constexpr int kPairLists = 5;
+// per-pair work lists of a batch: bucket_of | sorted | rerun | fbsorted | dbsorted | wlist
+constexpr int kPairLists = 6;
 struct FillPlan {
   KernelFn fn[kMaxFills];
   int occ[kMaxFills];
@@ -102,11 +103,12 @@ mica_status_t kernel_occupancy(int device, KernelFn fn, int threads, size_t shme
 
 // How many waves the band kernels of a plan may run with `bytes` of scratch
 // (a whole number of blocks, 0: not even one block), and the members of the
-// parameter block that follow.  `rerun`, `small`: the batch's re-run list
-// (free until the fills; it takes the planner's order) and table area.
+// parameter block that follow.  `rerun`, `wlist`, `small`: the batch's re-run
+// list (free until the fills; it takes the planner's order), a list of their
+// own and the table area.
 int64_t prune_slots(const FillPlan& fp, int n_cu, int64_t n_pairs, size_t bytes);
 void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_t fill_slots, uint32_t* rerun,
-                  uint32_t* small);
+                  uint32_t* wlist, uint32_t* small);
 
 // One kernel launch of a batch; `fill` marks the launches the timing events
 // bracket.

@@ -103,8 +103,8 @@ static_assert(kMaxM / kSeed < 256, "a part's number fits beside its bases");
 constexpr int kPruneParts = 2 * kNumModes;
 constexpr int kPruneItem = 8;          // pairs per item of the scan
 constexpr int kScanChunk = 8;          // items a wave of the scan takes, at most
-constexpr int kScanStaticWords = 192 + 3 * kPruneItem * kScanChunk;  // LDS words of a wave before its sequences (scan)
-constexpr int kBandStaticWords = 64;   // and before its band codes (band)
+constexpr int kScanStaticWords = 192 + 4 * kPruneItem * kScanChunk;  // LDS words of a wave before its sequences (scan)
+constexpr int kBandStaticWords = 128;   // and before its band codes (band)
 __host__ __device__ constexpr int prune_part(int kind, int mode) { return (kind == kK32 ? kNumModes : 0) + mode; }
 __host__ __device__ constexpr int prune_class(int pos) { return pos == 0 ? 16 : (pos == 1 ? 18 : (pos == 2 ? 17 : 18 - pos)); }
 // classes whose left pairs k_seed_left takes always (else: while they are few)
@@ -230,8 +230,10 @@ struct Params {
   uint32_t* lcount;            // [kNumBuckets] pairs left to k_seed_left
   int32_t left_full_;          // pairs left go to the full traceback without a fill (see left_full)
   int32_t left_waves;          // waves of its short-read launches (0: there are none)
-  uint32_t* nbcount;           // [kNumBuckets] pairs on the band lists, one strip
-  uint32_t* wbcount;           // [kNumBuckets] and more
+  uint32_t* nbcount;           // [kNumBuckets] pairs on the band lists, of up to 16 diagonals
+  uint32_t* w32count;          // [kNumBuckets] of 17-32
+  uint32_t* w64count;          // [kNumBuckets] of 33-64
+  uint32_t* wlist;             // [n_pairs] and the last of these lists, in the bucket's range
   uint32_t* pqstart;           // [kPruneParts][kNumClasses + 1] first queue item of each class
   uint64_t pr_slot_bytes, pr_rec_bytes;  // a wave's part of scratch, its band records
   int32_t pr_slots;

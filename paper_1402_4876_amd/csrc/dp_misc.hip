@@ -220,7 +220,8 @@ __device__ __forceinline__ void scan_tables(const Params* __restrict__ prm) {
     if (b < kNumBuckets) {
       prm->rcount[b] = prune_kind(bucket_kind(b)) ? 0u : acc;
       prm->nbcount[b] = 0;
-      prm->wbcount[b] = 0;
+      prm->w32count[b] = 0;
+      prm->w64count[b] = 0;
     }
   }
   if (b == 0) {

@@ -29,7 +29,7 @@ constexpr size_t al256(size_t x) { return (x + 255) / 256 * 256; }
 constexpr size_t kOffParams = 0;
 constexpr size_t kOffSmall = kOffParams + al256(sizeof(Params));
 constexpr size_t kOffClass = kOffSmall + al256(small::kWords * 4);
-constexpr size_t kOffPairs = kOffClass + al256(kMaxM + 1);  // bucket_of | sorted | rerun | fbsorted | dbsorted
+constexpr size_t kOffPairs = kOffClass + al256(kMaxM + 1);  // bucket_of | sorted | rerun | fbsorted | dbsorted | wlist
 constexpr size_t kOffSlots = kOffPairs + al256((size_t)kPairLists * kMaxPairs * 4);  // traceback slots
 static_assert(kOffSlots + (size_t(64) << 20) <= kScratchBytes, "room for the traceback slots");
 static_assert(sizeof(Params) % 4 == 0, "parameter block copied as words");
@@ -159,7 +159,7 @@ mica_status_t mica_dp_align_batch_noalloc(const mica_batch_t* b, const mica_scor
   P.n_slots = (int32_t)slots;
   queue_order(a.qorder, P.persist_q);
   const int64_t pr_waves = prune_slots(fp, ds.n_cu, b->n_pairs, area);
-  if (pr_waves > 0) prune_params(&P, fp, ds.n_cu, pr_waves, slots, P.rerun, sm);
+  if (pr_waves > 0) prune_params(&P, fp, ds.n_cu, pr_waves, slots, P.rerun, pairs + 5 * kMaxPairs, sm);
   const Params* dp = (const Params*)(ds.base + kOffParams);
 
   hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(256), 0, stream, a, ds.base);

@@ -350,8 +350,8 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   S.pr_raw_off = kBandStaticWords + (int)align_up((size_t)4 * S.pr_group_words, 4);
   S.pr_raw_words = 2 * ((m + 15) / 16 + (m + kBandMaxW + 15) / 16);
   S.pr_band_words = S.pr_raw_off + (int)align_up((size_t)4 * S.pr_raw_words, 4);
-  // direction bits of up to 4 strips, two rows a word; CIGAR staging of 8 pairs
-  S.pr_rec_bytes = traced ? (uint64_t)(m / 2 + 1) * 1024 : 0;
+  // direction bits of 64 lanes, two rows a word; CIGAR staging of 8 pairs
+  S.pr_rec_bytes = traced ? (uint64_t)(m / 2 + 1) * 256 : 0;
   S.pr_slot_bytes = std::max<uint64_t>(
       align_up(S.pr_rec_bytes + (traced ? (size_t)8 * (size_t)(m + n + 2) * 4 : 0), 256), 256);
   // blocks of four waves, or fewer where their LDS would pass 64 KB (rounded,
@@ -431,7 +431,7 @@ static int64_t left_short_waves(const FillPlan& fp, int n_cu, int64_t n_pairs, i
 }
 
 void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_t fill_slots, uint32_t* rerun,
-                  uint32_t* small) {
+                  uint32_t* wlist, uint32_t* small) {
   P->lcount = small + small::kLcount;
   P->left_waves = (int32_t)left_short_waves(fp, n_cu, P->n_pairs, fill_slots);
   P->pr_chunk = scan_chunk(n_cu, P->n_pairs);
@@ -439,7 +439,9 @@ void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_
   P->presorted = rerun;
   P->rcount = small + small::kRcount;
   P->nbcount = small + small::kNbcount;
-  P->wbcount = small + small::kWbcount;
+  P->w32count = small + small::kW32count;
+  P->w64count = small + small::kW64count;
+  P->wlist = wlist;
   P->pqstart = small + small::kPqstart;
   P->left_full_ = S.left_full_;
   P->pr_slot_bytes = S.pr_slot_bytes;
@@ -827,7 +829,7 @@ mica_status_t mica_dp_align_batch(mica_ctx_t c, const mica_batch_t* b, const mic
   P.stage_stride = sh.stage_stride;
   P.n_slots = (int32_t)slots;
   for (int i = 0; i < kQueueParts; ++i) P.persist_q[i] = c->persist_q[i];
-  if (pr_want > 0) prune_params(&P, fp, c->n_cu, pr_want, slots, P.rerun, c->d_small);
+  if (pr_want > 0) prune_params(&P, fp, c->n_cu, pr_want, slots, P.rerun, c->d_pairs + 5 * c->pair_cap, c->d_small);
   Params* dp = c->d_params + rp;
   HIP_TRY(hipMemcpyAsync(dp, &P, sizeof(Params), hipMemcpyHostToDevice, stream));
   HIP_TRY(hipEventRecord(c->ev[rp], stream));

@@ -70,15 +70,17 @@ __host__ __device__ constexpr int band_waves(int kind, int mode, bool trace) { r
 // the first 16 occurrences.
 constexpr int kPrHits = 16;
 constexpr int kPrPair = 8 + kPrHits;
-// And of a wave: the pairs it will add to the three lists (left, one strip,
-// more strips).
+// And of a wave: the pairs it will add to the four lists (left, bands of up to
+// 16, 32 and 64 diagonals).
 constexpr int kPrOutOff = 8 * kPrPair;
 constexpr int kPrOut = kPruneItem * kScanChunk;
-static_assert(kPrOutOff + 3 * kPrOut == kScanStaticWords, "the host sizes the LDS by this");
-// A band kernel's: the pairs to align again, {pair, band, core}.
-constexpr int kBandAgain = 16;
+static_assert(kPrOutOff + 4 * kPrOut == kScanStaticWords, "the host sizes the LDS by this");
+// A band kernel's: the item's pairs and the pairs to align again, an entry
+// {pair, band, core} each.
+constexpr int kBandItem = 8;
+constexpr int kBandAgain = 16;  // of up to 32 diagonals, and as many of up to 64
 constexpr int kBandEntry = 3;
-static_assert(kBandAgain * kBandEntry <= kBandStaticWords, "the host sizes the LDS by this");
+static_assert((kBandItem + 2 * kBandAgain) * kBandEntry <= kBandStaticWords, "the host sizes the LDS by this");
 
 // A listed pair's band: lowest diagonal, diagonals on both sides of the core
 // (kProven: nothing to check afterwards), strips.
@@ -182,7 +184,7 @@ template <class V>
 __device__ __forceinline__ bool band_fits(const Params* __restrict__ prm, int m, int n, int h0) {
   if constexpr (V::kPairs == 1) return true;
   const long top = (long)h0 + (long)prm->sa * (m < n ? m : n);
-  const long off = 16L * prm->se + prm->so;
+  const long off = 64L * prm->se + prm->so;
   // (the least value of a cell, and kMaxM dummy rows)
   const long low = 2L * prm->so + (long)(m + 1) * prm->se + kMaxM;
   return top + off <= 32767 && off <= 32767 && low <= 32767;
@@ -190,9 +192,10 @@ __device__ __forceinline__ bool band_fits(const Params* __restrict__ prm, int m,
 
 // The list of the pairs left and the list of bands, each in a bucket's range:
 // the two lists the fills use later, the left pairs in the one they are read
-// from (left_full of the planner).  Bands of one strip go from the start of
-// the range up, wider ones from its end down; their bands and cores lie in
-// arrays by pair that are free between the planner and the fills.
+// from (left_full of the planner).  Bands of up to 16 diagonals go from the
+// start of the range up, of up to 32 from its end down, wider ones to a list of
+// their own; their bands and cores lie in arrays by pair that are free between
+// the planner and the fills.
 template <int MODE, bool TRACE>
 __device__ __forceinline__ MICA_GLOBAL uint32_t* left_list(const Params* __restrict__ prm) {
   return G(TRACE && left_full(prm, MODE) ? prm->fbsorted : prm->sorted);
@@ -201,8 +204,8 @@ template <int MODE, bool TRACE>
 __device__ __forceinline__ MICA_GLOBAL uint32_t* band_list(const Params* __restrict__ prm) {
   return G(TRACE && left_full(prm, MODE) ? prm->sorted : prm->fbsorted);
 }
-// Adds the pairs of the lanes with `mine` to list li (0 left, 1 one strip, 2
-// more) of the wave's output.
+// Adds the pairs of the lanes with `mine` to list li (0 left, then the bands by
+// width) of the wave's output.
 __device__ __forceinline__ void put_out(uint32_t* lds, int li, int* cnt, bool mine, uint32_t p) {
   const uint64_t bal = __ballot(mine);
   if (mine) {
@@ -219,20 +222,23 @@ __device__ __forceinline__ void flush_out(const Params* __restrict__ prm, int bu
   const int lane = threadIdx.x & 63;
   lds_wait();
   const uint32_t bs = G(prm->bstart)[bucket];
-  uint32_t b0 = 0, b1 = 0, b2 = 0;
+  uint32_t b0 = 0, b1 = 0, b2 = 0, b3 = 0;
   if (lane == 0) {
     if (cnt[0]) b0 = atomicAdd(&prm->rcount[bucket], (uint32_t)cnt[0]);
     if (cnt[1]) b1 = atomicAdd(&prm->nbcount[bucket], (uint32_t)cnt[1]);
-    if (cnt[2]) b2 = atomicAdd(&prm->wbcount[bucket], (uint32_t)cnt[2]);
+    if (cnt[2]) b2 = atomicAdd(&prm->w32count[bucket], (uint32_t)cnt[2]);
+    if (cnt[3]) b3 = atomicAdd(&prm->w64count[bucket], (uint32_t)cnt[3]);
   }
   b0 = wave_uniform(b0);
   b1 = wave_uniform(b1);
   b2 = wave_uniform(b2);
+  b3 = wave_uniform(b3);
   const uint32_t* out = lds + kPrOutOff;
   if (lane < cnt[0]) left_list<MODE, TRACE>(prm)[bs + b0 + lane] = out[lane];
   if (lane < cnt[1]) band_list<MODE, TRACE>(prm)[bs + b1 + lane] = out[kPrOut + lane];
   if (lane < cnt[2]) band_list<MODE, TRACE>(prm)[bs + G(prm->bcount)[bucket] - 1u - b2 - lane] = out[2 * kPrOut + lane];
-  cnt[0] = cnt[1] = cnt[2] = 0;
+  if (lane < cnt[3]) G(prm->wlist)[bs + b3 + lane] = out[3 * kPrOut + lane];
+  cnt[0] = cnt[1] = cnt[2] = cnt[3] = 0;
   lds_wait();
 }
 
@@ -553,8 +559,7 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
     } else {
       // the loss to expect: parts without an occurrence stand for
       // substitutions, two diagonals (or a tail full of mismatches) for a gap
-      // (u of T parts hit at random hold some u + u u / 2 T of them)
-      // (where a band that fails costs more than it may save: without a traceback)
+      // (scores alone: u of T parts hit at random hold some u + u u / 2 T)
       auto subs = [&](int u) -> int { return (sa - sb) * (TRACE ? u : u + u * u / (2 * T)); };
       int loss = subs(missed);
       if (core.span > 0) {
@@ -563,7 +568,11 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
         loss += so + 2 * se;
       }
       ns = 99;
-      if (loss_certain<MODE>(prm, T, loss)) ns = (core.span + 1 + 2 * loss_drift(prm, core, loss) + 15) >> 4;
+      // (scores alone: a band that fails costs more than it may save, and over 32
+      // diagonals nearly as much as the table)
+      if (loss_certain<MODE>(prm, T, TRACE ? loss : loss + loss / 4))
+        ns = (core.span + 1 + 2 * loss_drift(prm, core, loss) + 15) >> 4;
+      if (!TRACE && ns > 2) ns = 99;
       margin = ns <= 4 ? (16 * ns - (core.span + 1)) >> 1 : 0;
       lo = c0 - margin;
     }
@@ -575,7 +584,8 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
   }
   put_out(lds, 0, &cnt[0], valid && x == 0 && !direct && !go, (uint32_t)p);
   put_out(lds, 1, &cnt[1], x == 0 && go && ns <= 1, (uint32_t)p);
-  put_out(lds, 2, &cnt[2], x == 0 && go && ns > 1, (uint32_t)p);
+  put_out(lds, 2, &cnt[2], x == 0 && go && ns == 2, (uint32_t)p);
+  put_out(lds, 3, &cnt[3], x == 0 && go && ns > 2, (uint32_t)p);
   lds_wait();
   return __builtin_popcountll(__ballot(x == 0 && (direct || go)));
 }
@@ -609,7 +619,7 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
   uint32_t* const seen = &prm->counters[kCtrSeedTried];
   bool ask = true, rare = false;
   BandCount count{0, 0};
-  int cnt[3] = {0, 0, 0};
+  int cnt[4] = {0, 0, 0, 0};
   int mode = 0, bucket = -1;
   auto flush = [&]() {
     if (mode == 0) flush_out<0, TRACE>(prm, bucket, lds, cnt);
@@ -653,33 +663,31 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
   if constexpr (TRACE) band_count_flush(prm, count);
 }
 
-// A band item: `take` pairs of a list (AGAIN: of the wave's own, with their
-// bands), in bands of NS strips at most (NS = 1: exactly).
-template <class V, int MODE, bool TRACE, int NS, bool AGAIN>
-__device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const uint32_t* list, int take,
-                                           uint32_t* lds, uint8_t* slot, int* cnt, BandCount* count) {
+// A band item: the `take` pairs whose entries lie at the start of the wave's
+// LDS, bands of up to LG diagonals, a group of LG lanes per packed couple.
+// (A strip loop over 16-lane groups has a wide band's strips wait for each
+// other: 0.46 us a row of three strips, 0.13 us in one wave-wide pass.)
+template <class V, int MODE, bool TRACE, int LG>
+__device__ __forceinline__ void prune_band(const Params* __restrict__ prm, int take, uint32_t* lds, uint8_t* slot,
+                                           int* cnt, BandCount* count) {
   typedef typename V::T T;
   constexpr int NP = V::kPairs;
   constexpr bool LOCAL = (MODE == 1);
   constexpr bool EXT = (MODE == 2);
   constexpr bool TRACK = (MODE != 0);
   const int lane = threadIdx.x & 63;
-  const int bg = lane >> 4;
-  const int l = lane & 15;
-  // entry q: the pair, its band and core
-  auto pair_at = [&](int q) -> int { return (int)(AGAIN ? list[q * kBandEntry] : G(list)[q]); };
-  auto band_at = [&](int q, int p) -> uint32_t { return AGAIN ? list[q * kBandEntry + 1] : G(prm->bucket_of)[p]; };
-  auto core_at = [&](int q, int p) -> uint32_t { return AGAIN ? list[q * kBandEntry + 2] : G(prm->dbsorted)[p]; };
+  constexpr int NS = 1;
+  const int bg = lane / LG;
+  const int l = lane & (LG - 1);
   MICA_GLOBAL uint32_t* rec = (MICA_GLOBAL uint32_t*)slot;
   BandFind<T, NS> find;
-  int ns_u = NS;
   {
     const MICA_GLOBAL uint32_t* __restrict__ ref2b = G(prm->ref2b);
     const MICA_GLOBAL uint32_t* __restrict__ reads2b = G(prm->reads2b);
     int mm[NP], nn[NP], dlo[NP], W[NP], d0[NP], h0[NP];
     uint64_t wo[NP], ro[NP];
     bool act[NP];
-    int rows_l = 0, ns_l = 0, mr_l = 0, tail_l = -0x7FFFFFFF;
+    int rows_l = 0, mr_l = 0, tail_l = -0x7FFFFFFF;
 #pragma unroll
     for (int h = 0; h < NP; ++h) {
       const int q = bg * NP + h;
@@ -688,22 +696,19 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
       W[h] = 1;
       wo[h] = ro[h] = 0;
       if (act[h]) {
-        const int p = pair_at(q);
-        const uint32_t w1 = band_at(q, p);
+        const int p = (int)lds[q * kBandEntry];
+        const uint32_t w1 = lds[q * kBandEntry + 1];
         mm[h] = G(prm->read_len)[p];
         nn[h] = G(prm->win_len)[p];
         wo[h] = G(prm->win_off)[p];
         ro[h] = G(prm->read_off)[p];
         if constexpr (EXT) h0[h] = prm->ext_h0 ? G(prm->ext_h0)[p] : prm->ext_default_h0;
         dlo[h] = (int)(w1 & 0xFFFFu) - 32768;
-        const int ns = (int)(w1 >> 24);
-        W[h] = 16 * ns;
+        W[h] = 16 * (int)(w1 >> 24);
         rows_l = mm[h] > rows_l ? mm[h] : rows_l;
-        ns_l = ns > ns_l ? ns : ns_l;
       }
     }
     const int rows_u = wave_max_int(rows_l);
-    if (NS == 4) ns_u = wave_max_int(ns_l);
 #pragma unroll
     for (int h = 0; h < NP; ++h) {
       // all pairs end on the wave's last row (extensions start on its first)
@@ -732,7 +737,7 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
     uint32_t* gq = lds + kBandStaticWords + bg * prm->pr_group_words;
     uint16_t* gw = (uint16_t*)(gq + prm->pr_rows);
     uint32_t* const raw = lds + prm->pr_raw_off + bg * prm->pr_raw_words;
-    const int rw = (rows_u + 15) >> 4, ww = (rows_u + 16 * ns_u + 15) >> 4;
+    const int rw = (rows_u + 15) >> 4, ww = (rows_u + LG + 15) >> 4;
     const uint64_t ref_last = (prm->ref_len - 1) >> 4, reads_last = (prm->reads_len - 1) >> 4;
 #pragma unroll
     for (int h = 0; h < NP; ++h) {
@@ -740,18 +745,18 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
       // band's first on; positions outside read or window are never used
       uint32_t* const r = raw + h * (rw + ww);
       if (act[h]) {
-        for (int w = l; w < rw; w += 16) {
+        for (int w = l; w < rw; w += LG) {
           const int64_t at = (int64_t)ro[h] + 16 * w - find.top[h];
           r[w] = at + 15 >= 0 ? signed_word(reads2b, at, reads_last) : 0u;
         }
-        for (int w = l; w < ww; w += 16) {
+        for (int w = l; w < ww; w += LG) {
           const int64_t at = (int64_t)wo[h] + 16 * w + dlo[h] - 1;
           r[rw + w] = at + 15 >= 0 ? signed_word(ref2b, at, ref_last) : 0u;
         }
       }
     }
     lds_wait();
-    for (int i0 = l; i0 < rows_u; i0 += 16) {
+    for (int i0 = l; i0 < rows_u; i0 += LG) {
       uint32_t qs = 0;
 #pragma unroll
       for (int h = 0; h < NP; ++h) {
@@ -760,8 +765,8 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
       }
       gq[i0] = qs;
     }
-    const int ne = rows_u + 16 * ns_u;
-    for (int e = l; e < ne; e += 16) {
+    const int ne = rows_u + LG;
+    for (int e = l; e < ne; e += LG) {
       uint32_t w = 0;
 #pragma unroll
       for (int h = 0; h < NP; ++h) {
@@ -791,7 +796,7 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
       }
       find.lim[s] = pack(lim[0], lim[NP - 1]);
     }
-    band_refill<V, MODE, NS, TRACE, true>(prm, dlo, W, d0, h0, act, rows_u, ns_u, mr_u, tail_u, gq, gw, rec, &find);
+    band_refill<V, MODE, NS, TRACE, true, LG>(prm, dlo, W, d0, h0, act, rows_u, 1, mr_u, tail_u, gq, gw, rec, &find);
   }
   if constexpr (TRACE) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   lds_wait();
@@ -801,7 +806,7 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
   // The pairs' values are read again here (list, global arrays) rather than
   // kept across the rows.  The group's best: largest score, then smallest j,
   // then smallest i.
-  constexpr int X = 16 / NP;
+  constexpr int X = LG / NP;
   const int h_ = l / X;  // the pair this lane walks
   int p_ = 0, m_ = 0, n_ = 0, h0_ = 0, sc_ = 0, ie_ = 0, je_ = 0, dlo_ = 0, W_ = 0;
   uint32_t w1_ = 0, core_ = 0;
@@ -814,9 +819,9 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
     int p = 0, m = 0, n = 0, h0 = 0, dlo = 0, W = 0;
     uint32_t w1 = 0, cw = 0;
     if (act) {
-      p = pair_at(q);
-      w1 = band_at(q, p);
-      cw = core_at(q, p);
+      p = (int)lds[q * kBandEntry];
+      w1 = lds[q * kBandEntry + 1];
+      cw = lds[q * kBandEntry + 2];
       m = G(prm->read_len)[p];
       n = G(prm->win_len)[p];
       if constexpr (EXT) h0 = prm->ext_h0 ? G(prm->ext_h0)[p] : prm->ext_default_h0;
@@ -831,7 +836,7 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
     for (int s = 0; s < NS; ++s) {
       const int gl = 16 * s + l;
       const int dl = dlo + gl;
-      if (s < ns_u && act && gl < W) {
+      if (act && gl < W) {
         if (!LOCAL) {
           const int j = m + dl;
           const int v = V::get(find.end[s], h) + top;
@@ -854,13 +859,13 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
     auto reduce = [&](int b, int key, int* kout) -> int {
       int top = b;
 #pragma unroll
-      for (int d = 1; d < 16; d <<= 1) {
+      for (int d = 1; d < LG; d <<= 1) {
         const int o = __shfl_xor(top, d, 64);
         top = o > top ? o : top;
       }
       int k = b == top ? key : 0x7FFFFFFF;
 #pragma unroll
-      for (int d = 1; d < 16; d <<= 1) {
+      for (int d = 1; d < LG; d <<= 1) {
         const int o = __shfl_xor(k, d, 64);
         k = o < k ? o : k;
       }
@@ -928,29 +933,20 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
       left_list<MODE, TRACE>(prm)[G(prm->bstart)[bucket] + pos] = (uint32_t)p_;
     }
   }
-  if constexpr (AGAIN) {
-    // the rest of the wave's list to its front
-    lds_wait();
-    uint32_t* const own = lds;
-    const int rest = (*cnt - take) * kBandEntry;  // fewer than 64 words
-    uint32_t a = 0;
-    if (lane < rest) a = own[take * kBandEntry + lane];
-    lds_wait();
-    if (lane < rest) own[lane] = a;
-    *cnt -= take;
-    lds_wait();
-  }
   if constexpr (!EXT) {
-    const bool mine = lead && again;
-    const uint64_t bal = __ballot(mine);
-    if (mine) {
-      const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-      uint32_t* e = lds + (*cnt + (int)rank) * kBandEntry;
-      e[0] = (uint32_t)p_;
-      e[1] = w1_;
-      e[2] = core_;
+#pragma unroll
+    for (int li = 0; li < 2; ++li) {
+      const bool mine = lead && again && (ns2 <= 2) == (li == 0);
+      const uint64_t bal = __ballot(mine);
+      if (mine) {
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+        uint32_t* e = lds + (kBandItem + li * kBandAgain + cnt[li] + (int)rank) * kBandEntry;
+        e[0] = (uint32_t)p_;
+        e[1] = w1_;
+        e[2] = core_;
+      }
+      cnt[li] += __builtin_popcountll(bal);
     }
-    *cnt += __builtin_popcountll(bal);
   }
 
   // ---- outputs ---------------------------------------------------------------------
@@ -964,7 +960,7 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, const
       if (lead) band_count<V, MODE>(prm, m_, n_, h0_, sc_, ie_, je_, count);
       MICA_GLOBAL uint32_t* stg = (MICA_GLOBAL uint32_t*)(slot + prm->pr_rec_bytes) +
                                   (size_t)(bg * NP + h_) * (size_t)prm->stage_stride;
-      band_walk<V, MODE>(prm, rec, lds + kBandStaticWords + (bg * NP + h_) * kWalkStage, stg, ns_u * 64, p_, m_, n_, ie_, je_, dlo_, W_, top_);
+      band_walk<V, MODE, LG>(prm, rec, lds + kBandStaticWords + (bg * NP + h_) * kWalkStage, stg, 64, p_, m_, n_, ie_, je_, dlo_, W_, top_);
     } else {
       if (lead) G(prm->status)[p_] = 0;
     }
@@ -1041,21 +1037,24 @@ __global__ __launch_bounds__(256, band_waves(V::kPairs == 1 ? kK32 : kK16, MODE,
 k_seed_band(const Params* __restrict__ prm) {
   constexpr int KIND = V::kPairs == 1 ? kK32 : kK16;
   constexpr int PART = prune_part(KIND, MODE);
-  constexpr int PPI = 4 * V::kPairs;
+  constexpr int P16 = 4 * V::kPairs, P32 = 2 * V::kPairs, P64 = V::kPairs;  // pairs per item
   extern __shared__ uint32_t smem[];
   const int wave = uni((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const int waves = (int)(blockDim.x >> 6);
   const int slot_id = (int)blockIdx.x * waves + wave;
   if (slot_id >= prm->pr_slots) return;
-  // lane k: class position k % kNumClasses of the wide (first) or narrow list
-  static_assert(2 * kNumClasses <= 64, "a lane per class and list");
+  // lane k: class position k % kNumClasses of the list of up to 64 diagonals
+  // (first), 32, 16
+  static_assert(3 * kNumClasses <= 64, "a lane per class and list");
   uint32_t pairs = 0;
-  if (lane < 2 * kNumClasses) {
+  const uint32_t ppi = lane < kNumClasses ? P64 : (lane < 2 * kNumClasses ? P32 : P16);
+  if (lane < 3 * kNumClasses) {
     const int b = bucket_id(KIND, prune_class(lane % kNumClasses), MODE);
-    pairs = lane < kNumClasses ? G(prm->wbcount)[b] : G(prm->nbcount)[b];
+    const uint32_t* count_of = lane < kNumClasses ? prm->w64count : (lane < 2 * kNumClasses ? prm->w32count : prm->nbcount);
+    pairs = G(count_of)[b];
   }
-  const uint32_t mine = (pairs + PPI - 1) / PPI;
+  const uint32_t mine = (pairs + ppi - 1) / ppi;
   uint32_t upto = mine;  // items of this lane and the ones before
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -1070,29 +1069,54 @@ k_seed_band(const Params* __restrict__ prm) {
                                                                                : (uint32_t)prm->pr_slots;
   uint32_t* lds = smem + wave * prm->pr_band_words;
   uint8_t* slot = prm->scratch + (size_t)slot_id * prm->pr_slot_bytes;
-  int cnt = 0;  // pairs to align again
+  int cnt[2] = {0, 0};  // pairs to align again, with up to 32 and up to 64 diagonals
   BandCount count{0, 0};
   uint32_t item = (uint32_t)slot_id;
   for (;;) {
     const bool done = item >= total;
-    if (cnt >= PPI || (done && cnt > 0)) {
-      prune_band<V, MODE, TRACE, 4, true>(prm, lds, cnt < PPI ? cnt : PPI, lds, slot, &cnt, &count);
-      continue;
+    // what to align next: pairs again, in a full item or at the end, or the
+    // next item of the lists; its entries to the front of the LDS
+    int width, take;
+    const bool a32 = cnt[0] >= P32 || (done && cnt[0] > 0), a64 = cnt[1] >= P64 || (done && cnt[1] > 0);
+    if (a32 || a64) {
+      const int li = a32 ? 0 : 1;
+      const int have = a32 ? cnt[0] : cnt[1];
+      width = a32 ? 32 : 64;
+      take = a32 ? (have < P32 ? have : P32) : (have < P64 ? have : P64);
+      uint32_t* const own = lds + (kBandItem + li * kBandAgain) * kBandEntry;  // fewer than 64 words
+      const uint32_t e = lane < have * kBandEntry ? own[lane] : 0u;
+      lds_wait();
+      if (lane < take * kBandEntry) lds[lane] = e;
+      else if (lane < have * kBandEntry) own[lane - take * kBandEntry] = e;
+      if (a32) cnt[0] -= take;
+      else cnt[1] -= take;
+    } else {
+      if (done) break;
+      const int k = __builtin_popcountll(__ballot(upto <= item));
+      const int li = k / kNumClasses;  // 0: 64 diagonals, 1: 32, 2: 16
+      width = li == 0 ? 64 : (li == 1 ? 32 : 16);
+      const uint32_t per = li == 0 ? P64 : (li == 1 ? P32 : P16);
+      const uint32_t first = (item - ((uint32_t)__builtin_amdgcn_readlane((int)upto, k) -
+                                      (uint32_t)__builtin_amdgcn_readlane((int)mine, k))) * per;
+      const uint32_t have = (uint32_t)__builtin_amdgcn_readlane((int)pairs, k) - first;
+      take = (int)(have < per ? have : per);
+      const int b = bucket_id(KIND, prune_class(k - li * kNumClasses), MODE);
+      const uint32_t bs = G(prm->bstart)[b];
+      const MICA_GLOBAL uint32_t* list =
+          li == 0 ? G(prm->wlist) + bs + first
+                  : band_list<MODE, TRACE>(prm) + (li == 1 ? bs + G(prm->bcount)[b] - first - (uint32_t)take : bs + first);
+      if (lane < take) {
+        const uint32_t p = list[lane];
+        lds[lane * kBandEntry] = p;
+        lds[lane * kBandEntry + 1] = G(prm->bucket_of)[p];
+        lds[lane * kBandEntry + 2] = G(prm->dbsorted)[p];
+      }
+      item += stride;
     }
-    if (done) break;
-    const int k = __builtin_popcountll(__ballot(upto <= item));
-    const uint32_t first = (item - ((uint32_t)__builtin_amdgcn_readlane((int)upto, k) -
-                                    (uint32_t)__builtin_amdgcn_readlane((int)mine, k))) * PPI;
-    const uint32_t have = (uint32_t)__builtin_amdgcn_readlane((int)pairs, k) - first;
-    const int take = have < (uint32_t)PPI ? (int)have : PPI;
-    const bool wide = k < kNumClasses;
-    const int b = bucket_id(KIND, prune_class(wide ? k : k - kNumClasses), MODE);
-    const uint32_t bs = G(prm->bstart)[b];
-    const uint32_t* list = (const uint32_t*)band_list<MODE, TRACE>(prm) +
-                           (wide ? bs + G(prm->bcount)[b] - first - (uint32_t)take : bs + first);
-    if (wide) prune_band<V, MODE, TRACE, 4, false>(prm, list, take, lds, slot, &cnt, &count);
-    else prune_band<V, MODE, TRACE, 1, false>(prm, list, take, lds, slot, &cnt, &count);
-    item += stride;
+    lds_wait();
+    if (width == 16) prune_band<V, MODE, TRACE, 16>(prm, take, lds, slot, cnt, &count);
+    else if (width == 32) prune_band<V, MODE, TRACE, 32>(prm, take, lds, slot, cnt, &count);
+    else prune_band<V, MODE, TRACE, 64>(prm, take, lds, slot, cnt, &count);
   }
   if constexpr (TRACE) band_count_flush(prm, count);
 }
