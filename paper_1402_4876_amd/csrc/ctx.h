@@ -36,6 +36,7 @@ constexpr size_t kBstart = kNumBuckets;
 constexpr size_t kQstart = 2 * kNumBuckets;  // kNumBuckets + 1 entries
 constexpr size_t kQorder = 3 * kNumBuckets + 8;
 constexpr size_t kCounters = 4 * kNumBuckets + 8;
+static_assert((kCounters + kCtrSeed) % 2 == 0, "one 64-bit word");
 constexpr size_t kBhead = 4 * kNumBuckets + 8 + kNumCounters;
 constexpr size_t kScount = 5 * kNumBuckets + 8 + kNumCounters;
 constexpr size_t kSfill = kScount + kNumSubBuckets;

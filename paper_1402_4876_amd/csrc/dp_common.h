@@ -123,8 +123,10 @@ enum : int {
   kCtrPruneWide = kCtrSideHead + kPersistParts,  // pairs the band kernels finished or left to the full
   kCtrPruneMid,                                 // traceback, by band width: over 64 diagonals, 17-64
   kCtrPruneLeft,                                // pairs left to the full traceback
-  kCtrSeedTried,                                // scanned pairs of the items that report, and the
-  kCtrSeedFound,                                // ones of them answered or listed
+  // four sums of 16 bits (64 bits, aligned): scanned pairs of the items that
+  // report; ones of them answered or listed; likely to hold; with a core
+  kCtrSeed = (kCtrPruneLeft + 2) / 2 * 2,
+  kCtrSeedHigh,
   kNumCounters
 };
 

@@ -318,8 +318,10 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   if (flags & MICA_PLAIN_LAUNCH) return MICA_OK;
   // Scores alone take one pass of the fill: where that does not fill the GPU
   // several times over, one item's latency is the time of both ways (1,000
-  // pairs of 150 x 200 in 32 bits: 60 us in the fill, 170 us here).
-  if (!traced && b->n_pairs < 65536) return MICA_OK;
+  // pairs of 150 x 200 in 32 bits: 60 us in the fill, 170 us here), and a scan
+  // that finds the reads too noisy costs some 50 us (70,000 of 60 x 120, 6%
+  // errors: 261 us without it, 304 with it; 140,000 of 150 x 300: 1.20, 1.26 ms).
+  if (!traced && (b->n_pairs < 65536 || (double)b->n_pairs * b->max_read_len * b->max_win_len < 3e9)) return MICA_OK;
   // two parts at least to hope for an answer (local: three), four where that
   // saves no traceback
   const int parts = b->max_read_len / kSeed;
@@ -354,11 +356,11 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   S.pr_rec_bytes = traced ? (uint64_t)(m / 2 + 1) * 256 : 0;
   S.pr_slot_bytes = std::max<uint64_t>(
       align_up(S.pr_rec_bytes + (traced ? (size_t)8 * (size_t)(m + n + 2) * 4 : 0), 256), 256);
-  // blocks of four waves, or fewer where their LDS would pass 64 KB (rounded,
+  // blocks of four waves, or fewer where their LDS would pass 62 KB (rounded,
   // so that batches of similar bounds share their launch graph)
   auto block = [](int words, int* threads, size_t* shmem) {
     const size_t bytes = (size_t)words * 4;
-    *threads = bytes * 4 <= (size_t)65536 ? 256 : (bytes * 2 <= (size_t)65536 ? 128 : 64);
+    *threads = bytes * 4 <= (size_t)63488 ? 256 : (bytes * 2 <= (size_t)63488 ? 128 : 64);
     *shmem = align_up(bytes * (size_t)(*threads / 64), 2048);
   };
   block(S.pr_scan_words, &fp->scan_threads, &fp->scan_shmem);

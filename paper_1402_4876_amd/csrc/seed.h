@@ -63,6 +63,9 @@ namespace mica {
 
 // Resident waves per SIMD.
 constexpr int kScanWaves = 6;
+// waves that may report on their first item (the sums fit 16 bits)
+constexpr uint32_t kSeedReporters = 65536;
+static_assert(kSeedReporters / 16 * kPruneItem < 65536, "sums of 16 bits");
 __host__ __device__ constexpr int band_waves(int kind, int mode, bool trace) { return 4; }
 
 // The scan's LDS words of a pair before its window and read: {lowest, highest
@@ -214,36 +217,45 @@ __device__ __forceinline__ void put_out(uint32_t* lds, int li, int* cnt, bool mi
   }
   *cnt += __builtin_popcountll(bal);
 }
-// Moves the wave's output to the bucket's lists: one request per list and
-// wave (the counts of a bucket serve about one request in 12 ns, so one per
-// item would take longer than the scan).
+// The count of a bucket's list li.
+__device__ __forceinline__ uint32_t* out_count(const Params* __restrict__ prm, int li, int bucket) {
+  return (li == 0 ? prm->rcount : (li == 1 ? prm->nbcount : (li == 2 ? prm->w32count : prm->w64count))) + bucket;
+}
+// Moves the wave's output to the bucket's lists, from entry b[li] of list li.
 template <int MODE, bool TRACE>
-__device__ __forceinline__ void flush_out(const Params* __restrict__ prm, int bucket, const uint32_t* lds, int* cnt) {
+__device__ __forceinline__ void write_out(const Params* __restrict__ prm, int bucket, const uint32_t* lds,
+                                          const int cnt[4], const uint32_t b[4]) {
   const int lane = threadIdx.x & 63;
-  lds_wait();
   const uint32_t bs = G(prm->bstart)[bucket];
-  uint32_t b0 = 0, b1 = 0, b2 = 0, b3 = 0;
-  if (lane == 0) {
-    if (cnt[0]) b0 = atomicAdd(&prm->rcount[bucket], (uint32_t)cnt[0]);
-    if (cnt[1]) b1 = atomicAdd(&prm->nbcount[bucket], (uint32_t)cnt[1]);
-    if (cnt[2]) b2 = atomicAdd(&prm->w32count[bucket], (uint32_t)cnt[2]);
-    if (cnt[3]) b3 = atomicAdd(&prm->w64count[bucket], (uint32_t)cnt[3]);
-  }
-  b0 = wave_uniform(b0);
-  b1 = wave_uniform(b1);
-  b2 = wave_uniform(b2);
-  b3 = wave_uniform(b3);
   const uint32_t* out = lds + kPrOutOff;
-  if (lane < cnt[0]) left_list<MODE, TRACE>(prm)[bs + b0 + lane] = out[lane];
-  if (lane < cnt[1]) band_list<MODE, TRACE>(prm)[bs + b1 + lane] = out[kPrOut + lane];
-  if (lane < cnt[2]) band_list<MODE, TRACE>(prm)[bs + G(prm->bcount)[bucket] - 1u - b2 - lane] = out[2 * kPrOut + lane];
-  if (lane < cnt[3]) G(prm->wlist)[bs + b3 + lane] = out[3 * kPrOut + lane];
-  cnt[0] = cnt[1] = cnt[2] = cnt[3] = 0;
+  if (lane < cnt[0]) left_list<MODE, TRACE>(prm)[bs + b[0] + lane] = out[lane];
+  if (lane < cnt[1]) band_list<MODE, TRACE>(prm)[bs + b[1] + lane] = out[kPrOut + lane];
+  if (lane < cnt[2]) band_list<MODE, TRACE>(prm)[bs + G(prm->bcount)[bucket] - 1u - b[2] - lane] = out[2 * kPrOut + lane];
+  if (lane < cnt[3]) G(prm->wlist)[bs + b[3] + lane] = out[3 * kPrOut + lane];
+}
+template <bool TRACE>
+__device__ __forceinline__ void write_out(const Params* __restrict__ prm, int mode, int bucket, const uint32_t* lds,
+                                          const int cnt[4], const uint32_t b[4]) {
+  if (mode == 0) write_out<0, TRACE>(prm, bucket, lds, cnt, b);
+  else if (mode == 1) write_out<1, TRACE>(prm, bucket, lds, cnt, b);
+  else write_out<2, TRACE>(prm, bucket, lds, cnt, b);
+}
+// All the wave listed goes to list 0, the pairs left.
+__device__ __forceinline__ void all_left(uint32_t* lds, int cnt[4]) {
+  const int lane = threadIdx.x & 63;
+  uint32_t* out = lds + kPrOutOff;
+  lds_wait();
+  for (int li = 1; li < 4; ++li) {
+    if (lane < cnt[li]) out[cnt[0] + lane] = out[li * kPrOut + lane];
+    cnt[0] += cnt[li];
+    cnt[li] = 0;
+  }
   lds_wait();
 }
 
 // The scan of an item of up to 8 pairs (8 lanes each) of one bucket; how many
-// of them it answered or put on a list.
+// of them it answered or listed for a band, how many of those are likely to
+// hold (bits 8 up) and how many had a core at all (bits 16 up).
 template <class V, int MODE, bool TRACE>
 __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const uint32_t* pairs, int np, int bucket,
                                           uint32_t* lds, int* cnt, BandCount* count) {
@@ -587,7 +599,11 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
   put_out(lds, 2, &cnt[2], x == 0 && go && ns == 2, (uint32_t)p);
   put_out(lds, 3, &cnt[3], x == 0 && go && ns > 2, (uint32_t)p);
   lds_wait();
-  return __builtin_popcountll(__ballot(x == 0 && (direct || go)));
+  // (of reads that lost more than a third of their parts few bands hold;
+  // extensions know their band from the loss itself)
+  const bool likely = direct || (EXT ? ok : go && 3 * missed <= T);
+  return __builtin_popcountll(__ballot(x == 0 && (direct || go))) | __builtin_popcountll(__ballot(x == 0 && likely)) << 8 |
+         __builtin_popcountll(__ballot(x == 0 && ok)) << 16;
 }
 
 // The scan of every pair of the batch, pr_chunk items of 8 pairs per wave:
@@ -605,7 +621,6 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
   const uint32_t chunk = (uint32_t)prm->pr_chunk;
   uint32_t it = qs[0] + w * chunk;
   const uint32_t end = it + chunk < total ? it + chunk : total;
-  if (it >= total) return;
   // lane: a mode's class position and its first item
   static_assert(kNumModes * kNumClasses <= 64, "a lane per mode and class");
   const bool in = lane < kNumModes * kNumClasses;
@@ -614,36 +629,58 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
 
   // A batch of unrelated pairs would pay for scans that find nothing: one wave
   // in 16 reports what its first item gave, and while that is less than one
-  // pair in eight, seven of eight items pass unseen.  (Read at the start and
-  // after an item that gave nothing: every read goes past the L2.)
-  uint32_t* const seen = &prm->counters[kCtrSeedTried];
-  bool ask = true, rare = false;
+  // pair in eight, seven of eight items pass unseen.  (Read by a block at its
+  // start and by a wave after an item that gave little: every read goes past
+  // the L2.)
+  // Where a band saves less, for scores alone and for short reads, the others
+  // pass unseen altogether, and the batch is also left if most of the reads
+  // with a core hold too many errors (70,000 local reads of 60 x 120, 6%
+  // errors: 0.74 ms with their bands, 0.61 without; 2%: 0.38 and 0.41).
+  __shared__ int head[kWavesPerBlock][9];  // bucket, four counts, four list positions of each wave
+  __shared__ bool rare_at[2];  // the block's look at its start and at its end
+  const bool cut = !TRACE || prm->pr_rows < 96;
+  unsigned long long* const seen = (unsigned long long*)(prm->counters + kCtrSeed);
+  auto look = [&]() -> bool {
+    const uint64_t v = __hip_atomic_load(seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t tried = (uint32_t)v & 0xFFFFu, found = (uint32_t)v >> 16;
+    const uint32_t likely = (uint32_t)(v >> 32) & 0xFFFFu, cores = (uint32_t)(v >> 48);
+    return tried >= 64u && (8u * found < tried || (cut && 2u * likely < cores));
+  };
+  const bool reporter = (w & 15u) == 0 && w < kSeedReporters;
+  if (threadIdx.x == 0) rare_at[0] = look();
+  __syncthreads();
+  bool ask = false, rare = rare_at[0];
   BandCount count{0, 0};
   int cnt[4] = {0, 0, 0, 0};
   int mode = 0, bucket = -1;
-  auto flush = [&]() {
-    if (mode == 0) flush_out<0, TRACE>(prm, bucket, lds, cnt);
-    else if (mode == 1) flush_out<1, TRACE>(prm, bucket, lds, cnt);
-    else flush_out<2, TRACE>(prm, bucket, lds, cnt);
-  };
   for (; it < end; ++it) {
-    if (ask) {
-      const uint32_t tried = __hip_atomic_load(&seen[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const uint32_t found = __hip_atomic_load(&seen[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      rare = tried >= 64u && 8u * found < tried;
-      ask = false;
-    }
+    if (ask && !(cut && rare)) rare = look();
+    ask = false;
     const int pos = __builtin_popcountll(__ballot(in && starts <= it)) - 1;
     const int md = pos / kNumClasses;
     const int b = bucket_id(KIND, prune_class(pos - md * kNumClasses), md);
-    if (b != bucket && bucket >= 0) flush();
+    if (b != bucket && bucket >= 0) {
+      // another bucket: what the wave has of this one goes by itself
+      lds_wait();
+      uint32_t at[4];
+#pragma unroll
+      for (int li = 0; li < 4; ++li) {
+        at[li] = 0;
+        if (lane == 0 && cnt[li]) at[li] = atomicAdd(out_count(prm, li, bucket), (uint32_t)cnt[li]);
+        at[li] = wave_uniform(at[li]);
+      }
+      write_out<TRACE>(prm, mode, bucket, lds, cnt, at);
+      cnt[0] = cnt[1] = cnt[2] = cnt[3] = 0;
+      lds_wait();
+    }
     mode = md;
     bucket = b;
     const uint32_t first = (it - (uint32_t)__builtin_amdgcn_readlane((int)starts, pos)) * kPruneItem;
     const uint32_t left = G(prm->bcount)[b] - first;
     const uint32_t* pairs = prm->presorted + G(prm->bstart)[b] + first;
     const int np = left < (uint32_t)kPruneItem ? (int)left : kPruneItem;
-    if (rare && (it & 7u) != 0) {
+    const bool report = reporter && it % chunk == 0;
+    if (rare && (cut ? !report : (it & 7u) != 0)) {
       uint32_t p = 0;
       if (lane < np) p = G(pairs)[lane];
       put_out(lds, 0, &cnt[0], lane < np, p);
@@ -652,14 +689,49 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
       if (md == 0) got = prune_scan<V, 0, TRACE>(prm, pairs, np, b, lds, cnt, &count);
       else if (md == 1) got = prune_scan<V, 1, TRACE>(prm, pairs, np, b, lds, cnt, &count);
       else got = prune_scan<V, 2, TRACE>(prm, pairs, np, b, lds, cnt, &count);
-      ask = got == 0;
-      if ((w & 15u) == 0 && it % chunk == 0 && lane == 0) {
-        atomicAdd(&seen[0], (uint32_t)np);
-        atomicAdd(&seen[1], (uint32_t)got);
-      }
+      const int found = got & 0xFF, likely = got >> 8 & 0xFF, cores = got >> 16;
+      ask = found == 0 || (cut && 2 * likely < cores);
+      if (report && lane == 0)
+        atomicAdd(seen, (unsigned long long)np | (unsigned long long)found << 16 | (unsigned long long)likely << 32 |
+                            (unsigned long long)cores << 48);
     }
   }
-  flush();
+
+  // The block's waves ask for room together: the counts of a bucket serve
+  // about one request in 12 ns, and a request per wave and list keeps them
+  // busy for 75 us in 400,000 pairs.
+  if (cut && threadIdx.x == 0) rare_at[1] = rare || look();
+  if (lane == 0) {
+    head[wave][0] = bucket;
+#pragma unroll
+    for (int li = 0; li < 4; ++li) head[wave][1 + li] = cnt[li];
+  }
+  __syncthreads();
+  const bool noisy = cut && rare_at[1];
+  int lead = wave;
+  uint32_t at[4] = {0, 0, 0, 0};
+  if (bucket >= 0) {
+    uint32_t before = 0, sum = 0;  // of lane li's list
+    for (int v = (int)(blockDim.x >> 6) - 1; v >= 0; --v) {
+      if (head[v][0] != bucket) continue;
+      uint32_t c = 0;
+      if (lane < 4) c = (uint32_t)head[v][1 + lane];
+      if (noisy) c = lane == 0 ? (uint32_t)(head[v][1] + head[v][2] + head[v][3] + head[v][4]) : 0u;
+      sum += c;
+      if (v < wave) before += c;
+      lead = v < lead ? v : lead;
+    }
+    if (lead == wave && lane < 4) head[wave][5 + lane] = sum ? (int)atomicAdd(out_count(prm, lane, bucket), sum) : 0;
+#pragma unroll
+    for (int li = 0; li < 4; ++li) at[li] = (uint32_t)__builtin_amdgcn_readlane((int)before, li);
+    if (noisy) all_left(lds, cnt);
+  }
+  __syncthreads();
+  if (bucket >= 0) {
+#pragma unroll
+    for (int li = 0; li < 4; ++li) at[li] += (uint32_t)head[lead][5 + li];
+    write_out<TRACE>(prm, mode, bucket, lds, cnt, at);
+  }
   if constexpr (TRACE) band_count_flush(prm, count);
 }
 

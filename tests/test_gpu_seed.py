@@ -31,6 +31,12 @@ def ctx():
     c.close()
 
 
+def add_noise(b, rate):
+    rng = np.random.default_rng(913)
+    flip = rng.random(len(b.reads)) < rate
+    b.reads[flip] = (b.reads[flip] + rng.integers(1, 4, int(flip.sum())).astype(b.reads.dtype)) % 4
+
+
 def seeded_batch(n_pairs, mode, m_lo, m_hi, seed):
     rng = np.random.default_rng([911, seed, mode, m_lo, m_hi])
     ref = synth.random_ref(rng, 60_000)
@@ -112,13 +118,28 @@ def test_sizes_of_items_and_launches(ctx, n_pairs):
         U.assert_same(U.run_gpu(ctx, b, sc, cap=8, clip=3, max_ext_h0=80), o, cap=8, what="mix of %d" % n_pairs)
 
 
+@pytest.mark.parametrize("noisy", [False, True])
 @pytest.mark.parametrize("mode", [0, 1, 2])
-def test_scores_alone_of_a_large_batch(ctx, mode):
-    """Without a traceback the band kernels take batches of 65,536 pairs or more."""
-    b = seeded_batch(2000, mode, 48, 90, 3).subset(np.tile(np.arange(2000), 33))
+def test_scores_alone_of_a_large_batch(ctx, mode, noisy):
+    """Without a traceback the band kernels take batches of 65,536 pairs and 3e9 cells or more, and leave those of
+    noisy reads."""
+    b = seeded_batch(2000, mode, 100, 160, 3)
+    if noisy:
+        add_noise(b, 0.12)
     o = U.run_oracle(b, trace=False, clip=5)
-    g = U.run_gpu(ctx, b, trace=False, clip=5, max_ext_h0=80 if mode == 2 else 0)
+    o = {k: np.tile(v, 100) for k, v in o.items() if k in U.KEYS_END + ("status",)}
+    g = U.run_gpu(ctx, b.subset(np.tile(np.arange(2000), 100)), trace=False, clip=5, max_ext_h0=80 if mode == 2 else 0)
     U.assert_same(g, o, trace=False, what="scores alone, mode %d" % mode)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_noisy_short_reads(ctx, mode):
+    """Traced reads under 96 bases with many errors: the scan stops, some blocks have listed bands by then."""
+    b = seeded_batch(3000, mode, 40, 90, 8)
+    add_noise(b, 0.12)
+    o = U.run_oracle(b)
+    o = {k: np.concatenate([v] * 20) for k, v in o.items()}
+    U.assert_same(U.run_gpu(ctx, b.subset(np.tile(np.arange(3000), 20))), o, what="noisy, mode %d" % mode)
 
 
 @pytest.mark.parametrize("mode", [0, 1, 2])
