@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "seed_bound.h"
+
 namespace mica {
 
 constexpr int kMaxM = 1024;  // longest read (rows)
@@ -94,11 +96,10 @@ __host__ __device__ constexpr int queue_part(int b) {
 
 constexpr uint32_t kSkip = 0xFFFFFFFFu;
 
-// The seeded band kernels (prune.h) take the packed 16-bit and the 32-bit
+// The seeded band kernels (seed.h) take the packed 16-bit and the 32-bit
 // buckets, one kernel per kind and mode (a "prune part").  Their queue runs
 // through a part's classes from the longest reads to the shortest, whatever
 // the plan's lanes, so that neighbouring items hold reads of similar length.
-constexpr int kSeed = 12;  // bases of a read part: 24 bits, and 8 for its number
 static_assert(kMaxM / kSeed < 256, "a part's number fits beside its bases");
 constexpr int kPruneParts = 2 * kNumModes;
 constexpr int kPruneItem = 8;          // pairs per item of the scan
@@ -244,9 +245,7 @@ struct Params {
   int32_t pr_win_words, pr_read_words, pr_part_words;  // scan: LDS words per pair
   int32_t pr_rows, pr_group_words;                     // band: rows, LDS words per group
   int32_t pr_raw_off, pr_raw_words;                    // and of its sequences
-  // twice the least loss that spoils a read part, and the same beside a gap
-  int32_t pr_cost2, pr_cost2_local, pr_leave2, pr_leave2_local;
-  int32_t pr_move2_del, pr_move2_ins;  // the same beside a run that may be split
+  SeedCosts pr_costs;          // what spoiling a read part costs
   uint32_t persist_q[kQueueParts];  // queue positions [persist_q[q], persist_q[q+1]) of queue part q
 };
 

@@ -297,18 +297,6 @@ mica_status_t kernel_occupancy(int device, KernelFn fn, int threads, size_t shme
 
 namespace {
 
-// Twice the least loss per spoiled read part (prune.h): a substitution or a
-// deletion spoils one part; an insertion run of L bases that touches s parts
-// has L >= 1, 2, 2 + (s - 2) kSeed, ... and costs o + L (a + e) for the s.
-int spoil_cost2(const mica_scoring_t& s) {
-  int c2 = 2 * std::min(s.match - s.mismatch, s.gap_open + s.gap_extend);
-  for (int k = 1; k <= kMaxM / kSeed; ++k) {
-    const int len = k <= 2 ? k : 2 + (k - 2) * kSeed;
-    c2 = std::min(c2, 2 * (s.gap_open + len * (s.match + s.gap_extend)) / k);
-  }
-  return c2;
-}
-
 // The band kernels of a batch.  Plain launches compute every table in full
 // (they are what the band kernels are compared with), and reads too short
 // for a certificate only pay for the scan.
@@ -332,16 +320,7 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   Params& S = fp->prune_shape;
   std::memset(&S, 0, sizeof(S));
   const int m = b->max_read_len, n = b->max_win_len;
-  S.pr_cost2 = spoil_cost2(s);
-  S.pr_cost2_local = std::min(S.pr_cost2, 2 * kSeed * s.match);
-  // off the diagonal, next to the gap that led there: an inserted run may have
-  // spoiled whole parts, each with its kSeed bases
-  S.pr_leave2 = std::min(S.pr_cost2, 2 * kSeed * (s.match + s.gap_extend));
-  S.pr_leave2_local = std::min(S.pr_cost2_local, S.pr_leave2);
-  // (a clipped end spoils its further parts with kSeed bases each)
-  const int move2 = std::min(S.pr_leave2, 2 * kSeed * s.match);
-  S.pr_move2_del = std::min(move2, 2 * s.gap_open);
-  S.pr_move2_ins = std::min(move2, s.gap_open);
+  S.pr_costs = seed_costs(s.match, s.mismatch, s.gap_open, s.gap_extend, kMaxM / kSeed);
   S.pr_win_words = (n + 15) / 16 + 2;
   S.pr_read_words = (m + 15) / 16 + 1;
   S.pr_part_words = std::max(4, (m / kSeed + 3) / 4 * 4);
@@ -458,12 +437,7 @@ void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_
   P->pr_group_words = S.pr_group_words;
   P->pr_raw_off = S.pr_raw_off;
   P->pr_raw_words = S.pr_raw_words;
-  P->pr_cost2 = S.pr_cost2;
-  P->pr_cost2_local = S.pr_cost2_local;
-  P->pr_leave2 = S.pr_leave2;
-  P->pr_leave2_local = S.pr_leave2_local;
-  P->pr_move2_del = S.pr_move2_del;
-  P->pr_move2_ins = S.pr_move2_ins;
+  P->pr_costs = S.pr_costs;
 }
 
 void launch_sequence(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t slots, int64_t pr_slots,

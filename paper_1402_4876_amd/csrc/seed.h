@@ -2,28 +2,22 @@
 // whole answer provably lies in a narrow band of diagonals are finished here,
 // before the fills, without computing the rest of their tables.
 //
-// What is proven.  Let a be the match score and call a m - score the loss of
-// an alignment of a read of m bases.  Substitutions (a - b each), insertion
-// runs (o + L (a + e)), deletion runs (o + L e) and clipped bases (a each)
-// all add to it.  Cut the read into T = m / kSeed parts of kSeed bases.  An
-// alignment in which no part is matched exactly along one diagonal spoils
-// every part, and spoiling k parts costs at least k c (spoil_cost2 in the
-// host runtime; in local mode the two clipped ends may spoil one part each
-// for free).  So an alignment of loss L < T c runs through an exact
-// occurrence of some part.  The scan finds all occurrences of all parts in
-// the window, every position against every part; the diagonals c0..c1 they
-// span are the pair's core.
+// What is proven.  Call a m - score the loss of an alignment of a read of m
+// bases, a the match score, and cut the read into T = m / kSeed parts of kSeed
+// bases.  An alignment in which no part is matched exactly along one diagonal
+// spoils every part, and spoiling k parts costs at least k c (seed_bound.h; in
+// local mode the two clipped ends may spoil one part each for free).  So an
+// alignment of loss L < T c runs through an exact occurrence of some part.
+// The scan finds all occurrences of all parts in the window, every position
+// against every part; the diagonals c0..c1 they span are the pair's core.
 //
 // Bands.  A part without any occurrence is spoiled in every alignment, so an
-// alignment that also moves w diagonals off the core loses at least the run
-// that moves it, o + w e (deletions) or o + w (a + e) (insertions), and c for
-// every such part but the one (two) that run touches; splitting the run
-// costs o for each part saved (two for insertions), hence min(c, o) and
-// min(c, o / 2) in place of c.  With occurrences on exactly two diagonals s
-// apart, h of them at least on each, an alignment through both pays that gap
+// alignment that also moves w diagonals off the core loses the deleted or
+// inserted bases of that move, its gap open, and c for every such part that
+// the move's own runs do not spoil.  With occurrences on exactly two diagonals
+// s apart, h of them at least on each, an alignment through both pays that gap
 // too, and one through a single diagonal spoils the other's h parts as well.
-// In local mode a clipped end spoils the first or the last part for free and
-// the others for kSeed a.  X(L) is the largest w this leaves for a loss L.
+// X(L) is the largest w this leaves for a loss L (loss_drift, with the cases).
 // If a band holds X(L) diagonals on both sides of the core, where L < T c is
 // the loss of the best alignment inside it, then every alignment that scores
 // as much lies in the band: score, end cell and its ties are the full
@@ -130,54 +124,6 @@ __device__ __forceinline__ int sum8(int v) {
 #pragma unroll
   for (int d = 1; d < 8; d <<= 1) v += __shfl_xor(v, d, 64);
   return v;
-}
-
-// The core of a pair: its diagonals' span; the fewer occurrences of the two
-// when they are exactly two diagonals (else 0); the parts without occurrence
-// (local: but for the first and the last).
-struct Core {
-  int span, hmin, missed;
-};
-__device__ __forceinline__ uint32_t core_word(const Core& c) {
-  return (uint32_t)c.span | ((uint32_t)c.hmin << 8) | ((uint32_t)c.missed << 16);
-}
-__device__ __forceinline__ Core core_of(uint32_t w) {
-  return Core{(int)(w & 0xFFu), (int)((w >> 8) & 0xFFu), (int)(w >> 16)};
-}
-
-// Diagonals an alignment of loss `loss` can move off the core (the bounds
-// above, with losses doubled).
-__device__ __forceinline__ int loss_drift(const Params* __restrict__ prm, const Core& c, int loss) {
-  const int a = prm->sa, so = prm->so, se = prm->se;
-  const int cd = prm->pr_move2_del, ci = prm->pr_move2_ins;
-  auto rest = [](int parts, int per) { return parts > 0 ? parts * per : 0; };
-  auto runs = [](int left2, int per) { return left2 >= 2 * per ? left2 / (2 * per) : 0; };
-  const int l2 = 2 * (loss - so);
-  const int parts = c.missed + c.hmin;
-  int w = runs(l2 - rest(parts - 1, cd), se);
-  int v = runs(l2 - rest(parts - 2, ci), a + se);
-  w = v > w ? v : w;
-  if (c.hmin > 0) {
-    // the two diagonals' gap as a deletion or an insertion, then the move
-    const int free = c.span > 1 ? 2 : 1;
-    const int td = l2 - 2 * (so + c.span * se), ti = l2 - 2 * (so + c.span * (a + se));
-    v = runs(td - rest(c.missed - 2, cd), se);
-    w = v > w ? v : w;
-    v = runs(td - rest(c.missed - 3, ci), a + se);
-    w = v > w ? v : w;
-    v = runs(ti - rest(c.missed - free - 1, ci), se);
-    w = v > w ? v : w;
-    v = runs(ti - rest(c.missed - free - 2, ci), a + se);
-    w = v > w ? v : w;
-  }
-  return w;
-}
-
-// The certificate of T parts: can an alignment of this loss avoid them all?
-template <int MODE>
-__device__ __forceinline__ bool loss_certain(const Params* __restrict__ prm, int T, int loss) {
-  const int parts = MODE == 1 ? T - 2 : T;
-  return parts > 0 && 2 * loss < parts * (MODE == 1 ? prm->pr_cost2_local : prm->pr_cost2);
 }
 
 // The values every band item of a pair needs to be able to hold in 16 bits:
@@ -485,13 +431,10 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
   } else {
     bool leaves = false;  // leaving the diagonal might pay
     const int lose2 = 2 * (sa - sb);
-    const int cx2 = LOCAL ? prm->pr_leave2_local : prm->pr_leave2;
+    const int cx2 = LOCAL ? prm->pr_costs.leave2_local : prm->pr_costs.leave2;
     const int few = one && mism <= kPrHits ? mism : 0;
-    // the loss saved on read bases [from, to] with k mismatches, doubled: each
-    // part inside costs one spoiling (but those the gaps and a clipped end touch)
     auto saved2 = [&](int from, int to, int k, int free) -> int {
-      const int parts = ((to + 1) / kSeed < T ? (to + 1) / kSeed : T) - (from + kSeed - 1) / kSeed - free;
-      return lose2 * k - (parts > 0 ? parts * cx2 : 0);
+      return leave_saves2(lose2, cx2, T, from, to, k, free);
     };
     for (int i = x; i < few; i += 8) {
       const int pi = hit[i];
@@ -528,7 +471,7 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
         score = sa * m - (sa - sb) * mism;
         ie = m;
       }
-      direct = loss_certain<MODE>(prm, T, sa * m - score);
+      direct = loss_certain(prm->pr_costs, LOCAL, T, sa * m - score);
     }
   }
   // (ie = 0: the anchor itself, or a local read that matches nowhere)
@@ -562,7 +505,7 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
     if constexpr (EXT) {
       const long loss = (long)h0 + (long)sa * m - best + prm->ext_clip;
       const int lc = loss > (1 << 20) ? 1 << 20 : (int)loss;
-      const int xd = loss_drift(prm, core, lc);
+      const int xd = loss_drift(prm->pr_costs, core, lc);
       const int xi = lc >= so + sa + se ? (lc - so) / (sa + se) : 0;
       lo = -(xi < m ? xi : m);
       const int hi = xd < n ? xd : n;
@@ -582,10 +525,10 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
       ns = 99;
       // (scores alone: a band that fails costs more than it may save, and over 32
       // diagonals nearly as much as the table)
-      if (loss_certain<MODE>(prm, T, TRACE ? loss : loss + loss / 4))
-        ns = (core.span + 1 + 2 * loss_drift(prm, core, loss) + 15) >> 4;
+      if (loss_certain(prm->pr_costs, LOCAL, T, TRACE ? loss : loss + loss / 4))
+        ns = band_strips(core.span, loss_drift(prm->pr_costs, core, loss));
       if (!TRACE && ns > 2) ns = 99;
-      margin = ns <= 4 ? (16 * ns - (core.span + 1)) >> 1 : 0;
+      margin = ns <= 4 ? band_margin(core.span, ns) : 0;
       lo = c0 - margin;
     }
   }
@@ -991,13 +934,13 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, int t
     const Core core = core_of(core_);
     const int margin = (int)((w1_ >> 16) & 0xFFu);
     const int loss = prm->sa * m_ - sc_;
-    const bool sure = loss_certain<MODE>(prm, m_ / kSeed, loss);
-    const int drift = sure ? loss_drift(prm, core, loss) : 0;
+    const bool sure = loss_certain(prm->pr_costs, LOCAL, m_ / kSeed, loss);
+    const int drift = sure ? loss_drift(prm->pr_costs, core, loss) : 0;
     good = sure && drift <= margin;
     // a wider band will be (the loss can only shrink there)
-    ns2 = (core.span + 1 + 2 * drift + 15) >> 4;
+    ns2 = band_strips(core.span, drift);
     again = sure && !good && ns2 <= 4;
-    marg2 = (16 * ns2 - (core.span + 1)) >> 1;
+    marg2 = band_margin(core.span, ns2);
     if (lead && again) w1_ = band_word(dlo_ + margin - marg2, marg2, ns2);
     if (lead && !good && !again) {
       const int bucket = bucket_id(NP == 1 ? kK32 : kK16, prm->class_of_m[m_], MODE);
