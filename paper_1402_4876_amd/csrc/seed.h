@@ -299,7 +299,8 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
             atomicMin(&res[0], d);
             atomicMax(&res[1], d);
             const int at = atomicAdd(&res[2], 1);
-            if (at < kPrHits) hit[at] = d;
+            // (local: whether it is the first or the last part in the low bit)
+            if (at < kPrHits) hit[at] = LOCAL ? 2 * d + (z[t] == 0 || (int)z[t] == T - 1 ? 1 : 0) : d;
             atomicOr((uint32_t*)&res[4 + (z[t] >> 5)], 1u << (z[t] & 31u));
           }
         });
@@ -342,19 +343,23 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
       core.missed -= (m0 & 1u) ? 0 : 1;
       core.missed -= (last & 1u) ? 0 : 1;
     }
-    // (a part that occurs on both diagonals is spoiled by neither)
+    // (a part that occurs on both diagonals is spoiled by neither, and in local
+    // mode the first and the last are spoiled by clipping)
     if (ok && core.span > 0 && hits <= kPrHits && hits == T - missed) {
-      int at0 = 0, at1 = 0;
+      int at0 = 0, at1 = 0;  // occurrences, and of the parts that count from bit 8
 #pragma unroll
       for (int u = 0; u < kPrHits / 8; ++u) {
         const int k = x + 8 * u;
-        const int d = k < hits ? hit[k] : c0 + 1000;
-        at0 += d == c0 ? 1 : 0;
-        at1 += d == c1 ? 1 : 0;
+        const int v = k < hits ? hit[k] : (LOCAL ? 2 : 1) * (c0 + 1000);
+        const int d = LOCAL ? v >> 1 : v;
+        const int one = LOCAL && (v & 1) ? 1 : 0x101;
+        at0 += d == c0 ? one : 0;
+        at1 += d == c1 ? one : 0;
       }
       at0 = sum8(at0);
       at1 = sum8(at1);
-      core.hmin = at0 + at1 == hits ? (at0 < at1 ? at0 : at1) : 0;
+      const int h0 = at0 >> 8, h1 = at1 >> 8;
+      core.hmin = (at0 & 0xFF) + (at1 & 0xFF) == hits ? (h0 < h1 ? h0 : h1) : 0;
     }
   }
   // mismatches on the one diagonal, where it lies inside the window; their

@@ -76,7 +76,8 @@ inline SeedCosts seed_costs(int a, int b, int o, int e, int max_parts) {
 
 // The core of a pair: the span of the diagonals of its parts' occurrences; the
 // fewer occurrences of the two when they are exactly two diagonals (else 0);
-// the parts without occurrence (local: but for the first and the last).
+// the parts without occurrence.  In local mode the first and the last part, which
+// clipping spoils for nothing, count in neither.
 struct Core {
   int span, hmin, missed;
 };

@@ -153,12 +153,15 @@ static Found scan(const std::vector<int>& q, const std::vector<int>& w, bool loc
     if (!has[(size_t)s] && !(local && (s == 0 || s == f.T - 1))) f.core.missed++;
   }
   if (f.core.span > 0 && (int)hits.size() == occur) {
-    int at0 = 0, at1 = 0;
+    int on0 = 0, on1 = 0, at0 = 0, at1 = 0;
     for (const auto& h : hits) {
-      at0 += h.first == f.c0 ? 1 : 0;
-      at1 += h.first == f.c1 ? 1 : 0;
+      const int counts = local && (h.second == 0 || h.second == f.T - 1) ? 0 : 1;
+      on0 += h.first == f.c0 ? 1 : 0;
+      on1 += h.first == f.c1 ? 1 : 0;
+      at0 += h.first == f.c0 ? counts : 0;
+      at1 += h.first == f.c1 ? counts : 0;
     }
-    if (at0 + at1 == (int)hits.size()) f.core.hmin = std::min(at0, at1);
+    if (on0 + on1 == (int)hits.size()) f.core.hmin = std::min(at0, at1);
   }
   return f;
 }
@@ -240,7 +243,7 @@ static void check(const std::vector<int>& q, const std::vector<int>& w, const Sc
 }
 
 // Pairs whose best alignment a weaker bound missed: long insertions that
-// swallow parts.
+// swallow parts; end parts, which clipping spoils, on a diagonal of their own.
 struct Known {
   bool local;
   Scoring s;
@@ -260,6 +263,11 @@ static const Known known[] = {
      "CTTCGATGCTATAGCGAGCGTAACGGAGC",
      "CCGATGTATTCTAATACACCGCGAGTATCTCGACTAAATCATCTGCTCGTCTAAATGATATTTCTCCGGCTGAGTGGTCATAAGGCAGCTTTTGTTCGGAGTGTATGCCACCTC"
      "ATACCGATAGTCTAGGGTGGGATAGATGCTTCGATGCTATAGCGAGCGTAACGGAGCGAGAGCTTGGAC"},
+    {true, {1, -4, 6, 1},
+     "ATGTTGCGCCCGTGTAATCCTGGCTAAAAATATAGGACACACACCGCCAGGTCGGTGAACTCATCGCGACTGCGGATCTACCCTTTATCGTACCGTCTCTTATTTTGATATCGT"
+     "ACCGTCCTG",
+     "TAGACTTTCTATGCCTTCACAGGCCCTGGACCATGAGAAAGATAGCCATGTTGCGCCCGCTAATTGGAGGTTGTTGCGCCCGTGTAATCCTGGCTAAAAATATAGGACACACAC"
+     "CGCCAGGTCGGTGAACTCATCGCGACTGCGGATCTACCCTTTATCGTACCGTCTCTTATTTTGATAGGATAATCGTACCGTCCTGAAACTAAGTGCGAACAG"},
 };
 
 int main(int argc, char** argv) {
@@ -333,7 +341,32 @@ int main(int argc, char** argv) {
       if (pick(0, 1)) w.erase(w.begin() + at, w.begin() + std::min((int)w.size(), at + len));
       else for (int i = 0; i < len; ++i) w.insert(w.begin() + at, pick(0, 3));
     }
-    if ((int)w.size() < kSeed) continue;
+    if ((int)w.size() >= kSeed) check(q, w, s, local);
+
+    // the read in its place but for the first and the last part, which lie on a
+    // diagonal of their own (one of them as the read repeats it further in), and
+    // an end without its part beside
+    if (r % 4) continue;
+    const int T = m / kSeed, last = kSeed * (T - 1);
+    const int d = pick(0, 1) ? pick(1, 30) : -pick(1, 30);
+    for (int i = 0; i < kSeed; ++i) {
+      const int from = d > 0 ? i : last + i;
+      if (from + d >= 0 && from + d < m) q[(size_t)(from + d)] = q[(size_t)from];
+    }
+    s = common[rng() % 5];
+    w.assign((size_t)(m + 120), 0);
+    for (int& x : w) x = pick(0, 3);
+    lay(0, m, 60, 0);
+    for (int part : {0, last})
+      for (int t = pick(1, 3); t > 0; --t) {
+        int& x = w[(size_t)(60 + part + pick(0, kSeed - 1))];
+        x = (x + pick(1, 3)) & 3;
+      }
+    if (d > 0) lay(last, last + kSeed, 60 + d, 0);
+    else lay(0, kSeed, 60 + d, 0);
+    const int past = pick(0, 1) ? pick(1, 12) : -pick(1, 12);
+    if (pick(0, 1)) lay(last + pick(1, 4), m, 60 + past, 0);
+    else lay(0, kSeed - pick(1, 4), 60 + past, 0);
     check(q, w, s, local);
   }
   std::printf("%ld pairs: %d with a core, %d certain, %d at the edge, %d without a gap, %d failures\n", pairs, cored, certified,

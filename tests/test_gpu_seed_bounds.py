@@ -8,7 +8,8 @@ import synth
 
 pytestmark = pytest.mark.gpu
 
-# (mode, scoring, read, window): insertions of more than 13 bases, which swallow whole parts of the read
+# (mode, scoring, read, window): insertions of more than 13 bases, which swallow whole parts of the read; local, the
+# first and the last part (which clipping spoils for nothing) on a diagonal of their own
 PAIRS = [
     (0, (2, -20, 40, 2),
      "TCAGTTTATGCCCCCGTAGGCCCTAGTAGTATGCCAAGGCGTGCTTTCCTCCTCCCTTACTATGCAAACGCTCTGCAGATTTCGTCCAGATGCATATTGCGTCCG",
@@ -23,6 +24,11 @@ PAIRS = [
      "CTTCGATGCTATAGCGAGCGTAACGGAGC",
      "CCGATGTATTCTAATACACCGCGAGTATCTCGACTAAATCATCTGCTCGTCTAAATGATATTTCTCCGGCTGAGTGGTCATAAGGCAGCTTTTGTTCGGAGTGTATGCCACCTC"
      "ATACCGATAGTCTAGGGTGGGATAGATGCTTCGATGCTATAGCGAGCGTAACGGAGCGAGAGCTTGGAC"),
+    (1, (1, -4, 6, 1),
+     "ATGTTGCGCCCGTGTAATCCTGGCTAAAAATATAGGACACACACCGCCAGGTCGGTGAACTCATCGCGACTGCGGATCTACCCTTTATCGTACCGTCTCTTATTTTGATATCGT"
+     "ACCGTCCTG",
+     "TAGACTTTCTATGCCTTCACAGGCCCTGGACCATGAGAAAGATAGCCATGTTGCGCCCGCTAATTGGAGGTTGTTGCGCCCGTGTAATCCTGGCTAAAAATATAGGACACACAC"
+     "CGCCAGGTCGGTGAACTCATCGCGACTGCGGATCTACCCTTTATCGTACCGTCTCTTATTTTGATAGGATAATCGTACCGTCCTGAAACTAAGTGCGAACAG"),
 ]
 
 
@@ -78,3 +84,33 @@ def test_insertion_near_an_end_of_a_nearly_periodic_window(ctx, scoring):
         windows.append(win)
     b = batch(reads, windows, 0)
     U.assert_same(U.run_gpu(ctx, b, scoring), U.run_oracle(b, scoring), what="insertions %s" % (scoring,))
+
+
+@pytest.mark.parametrize("scoring", [(1, -4, 6, 1), (1, -3, 5, 2), (2, -4, 4, 2)])
+def test_local_end_parts_on_a_diagonal_of_their_own(ctx, scoring):
+    rng = np.random.default_rng([932, -scoring[1]])
+    reads, windows = [], []
+    for _ in range(6000):
+        m, d = int(rng.integers(72, 160)), int(rng.integers(1, 30)) * int(rng.choice([-1, 1]))
+        q = rng.integers(0, 4, m).astype(np.uint8)
+        last = 12 * (m // 12 - 1)
+        # one end part as the read repeats it further in
+        for i in (range(0, 12) if d > 0 else range(last, last + 12)):
+            q[i + d] = q[i]
+        win = np.concatenate([rng.integers(0, 4, 60), q, rng.integers(0, 4, 60)]).astype(np.uint8)
+        for part in (0, last):                              # both spoiled in place
+            i = 60 + part + int(rng.integers(0, 12))
+            win[i] = (win[i] + rng.integers(1, 4)) % 4
+        if d > 0:                                           # the other on the same diagonal
+            win[60 + d + last: 60 + d + last + 12] = q[last: last + 12]
+        else:
+            win[60 + d: 60 + d + 12] = q[:12]
+        past, cut = int(rng.integers(1, 13)) * int(rng.choice([-1, 1])), int(rng.integers(1, 5))
+        if rng.random() < 0.5:                              # an end, without its part, a gap away
+            win[60 + past + last + cut: 60 + past + m] = q[last + cut:]
+        else:
+            win[60 + past: 60 + past + 12 - cut] = q[:12 - cut]
+        reads.append(q)
+        windows.append(win)
+    b = batch(reads, windows, 1)
+    U.assert_same(U.run_gpu(ctx, b, scoring), U.run_oracle(b, scoring), what="end parts %s" % (scoring,))

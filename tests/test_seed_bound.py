@@ -21,7 +21,7 @@ def check():
 
 
 @pytest.mark.parametrize("seed", [1, 2])
-@pytest.mark.parametrize("mode", ["semiglobal"])
+@pytest.mark.parametrize("mode", ["semiglobal", "local"])
 def test_best_alignments_stay_inside_the_bounds(check, mode, seed):
     r = subprocess.run([check, mode, str(seed), "25000"], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-4000:] + r.stderr[-2000:]
