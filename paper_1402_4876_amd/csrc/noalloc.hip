@@ -159,6 +159,8 @@ mica_status_t mica_dp_align_batch_noalloc(const mica_batch_t* b, const mica_scor
   P.n_slots = (int32_t)slots;
   queue_order(a.qorder, P.persist_q);
   const int64_t pr_waves = prune_slots(fp, ds.n_cu, b->n_pairs, area);
+  if (fp.n_prune > 0 && pr_waves == 0)
+    return fail(MICA_ERR_LIMIT, "windows too long for the allocation-free call's band slots");
   if (pr_waves > 0) prune_params(&P, fp, ds.n_cu, pr_waves, slots, P.rerun, pairs + 5 * kMaxPairs, sm);
   const Params* dp = (const Params*)(ds.base + kOffParams);
 

@@ -383,8 +383,8 @@ int64_t prune_slots(const FillPlan& fp, int n_cu, int64_t n_pairs, size_t bytes)
   int64_t slots = (int64_t)occ * n_cu * per_block;
   // the bands of a mode: at most one partial item per class and list
   slots = std::min(slots, (int64_t)align_up((size_t)(n_pairs / 4 + 2 * kNumClasses), (size_t)per_block));
-  // (a slot here is no larger than a fill's, so memory for a block of fills,
-  // without which the call fails, holds a block of these)
+  // (a slot and a block here are no larger than the fills', so the memory of a
+  // block of fills, which every call has, holds a block of these)
   return std::min(slots, (int64_t)(bytes / fp.prune_shape.pr_slot_bytes) / per_block * per_block);
 }
 
@@ -766,8 +766,12 @@ mica_status_t mica_dp_align_batch(mica_ctx_t c, const mica_batch_t* b, const mic
   if ((size_t)slots * sh.slot_bytes > c->ws_cap && slots > kWavesPerBlock)
     slots = (int64_t)(c->ws_cap / sh.slot_bytes) / kWavesPerBlock * kWavesPerBlock;
   if (slots < kWavesPerBlock) return fail(MICA_ERR_OUT_OF_MEMORY, "workspace too small for one block");
-  // the band kernels run before the fills, in the same memory
-  const int64_t pr_want = prune_slots(fp, c->n_cu, b->n_pairs, c->ws_cap);
+  // the band kernels run before the fills, in the same memory: under the cap, or
+  // in the one block of fills that a smaller cap still gets
+  const int64_t pr_want =
+      prune_slots(fp, c->n_cu, b->n_pairs, std::max(c->ws_cap, (size_t)slots * sh.slot_bytes));
+  // (the fills that the band kernels replace are not among the launches)
+  if (fp.n_prune > 0 && pr_want == 0) return fail(MICA_ERR_OUT_OF_MEMORY, "workspace too small for the band kernels");
   const size_t scratch_bytes =
       std::max((size_t)slots * sh.slot_bytes, (size_t)pr_want * (size_t)fp.prune_shape.pr_slot_bytes);
   st = ensure_scratch(c, scratch_bytes);
