@@ -233,17 +233,19 @@ mica_status_t build(mica_fm* f, const uint32_t* host_ref2b, uint64_t n) {
   f->ix.kmer_k = 0;
   const int k = fm_kmer_bases(n);
   void* tmp = nullptr;
-  if (k > 0 && hipMalloc(&f->d_kmer, (size_t)8 << (2 * k)) == hipSuccess) {
-    hipError_t e = hipMalloc(&tmp, (size_t)8 << (2 * (k > 1 ? k - 1 : 1)));
-    if (e == hipSuccess) e = fm_build_kmers(f->ix, k, (uint32_t*)f->d_kmer, (uint32_t*)tmp);
-    if (tmp) (void)hipFree(tmp);
+  auto alloc = [](size_t bytes) -> void* {
+    void* p = nullptr;
+    if (hipMalloc(&p, bytes) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+  };
+  if (fm_kmer_memory(k, alloc, [](void* p) { (void)hipFree(p); }, &f->d_kmer, &tmp)) {
+    const hipError_t e = fm_build_kmers(f->ix, k, (uint32_t*)f->d_kmer, (uint32_t*)tmp);
+    (void)hipFree(tmp);
     HIP_TRY(e);
     f->ix.kmer = (const uint32_t*)f->d_kmer;
     f->ix.kmer_k = k;
-    f->bytes += (uint64_t)8 << (2 * k);
-  } else if (k > 0) {
-    f->d_kmer = nullptr;
-    (void)hipGetLastError();
+    f->bytes += fm_kmer_bytes(k);
   }
   return MICA_OK;
 }

@@ -4,6 +4,8 @@
 
 #include <cstdint>
 
+#include "fm_table.h"
+
 struct mica_fm;
 
 namespace mica {
@@ -28,16 +30,8 @@ struct FmIndex {
 
 const FmIndex* fm_index_of(const mica_fm* f);
 
-// Bases of the table's strings: as many as keep it within twice the
-// reference's length in bytes, 12 at most (134 MB).
-constexpr int kFmMaxKmer = 12;
-inline int fm_kmer_bases(uint64_t n) {
-  int k = 0;
-  while (k < kFmMaxKmer && (8ull << (2 * (k + 1))) <= 2 * n) ++k;
-  return k;
-}
 // Fills table (4^k entries) from the index on its device, level by level (tmp:
-// another 4^k entries); waits for the result.
+// the 4^(k - 1) entries of the level below); waits for the result.
 hipError_t fm_build_kmers(const FmIndex& ix, int k, uint32_t* table, uint32_t* tmp);
 
 }  // namespace mica
