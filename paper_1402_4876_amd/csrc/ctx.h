@@ -36,7 +36,7 @@ constexpr size_t kBstart = kNumBuckets;
 constexpr size_t kQstart = 2 * kNumBuckets;  // kNumBuckets + 1 entries
 constexpr size_t kQorder = 3 * kNumBuckets + 8;
 constexpr size_t kCounters = 4 * kNumBuckets + 8;
-static_assert((kCounters + kCtrSeed) % 2 == 0, "one 64-bit word");
+static_assert((kCounters + kCtrSeed) % 2 == 0, "64-bit words");
 constexpr size_t kBhead = 4 * kNumBuckets + 8 + kNumCounters;
 constexpr size_t kScount = 5 * kNumBuckets + 8 + kNumCounters;
 constexpr size_t kSfill = kScount + kNumSubBuckets;
@@ -93,6 +93,10 @@ struct FillPlan {
   bool left_long_reads[2 * kNumModes];
   int n_left = 0;
   int left_pairs = 2;  // pairs per item
+  int left_buckets = 0;     // of short reads in use
+  int left_rounds = 4;      // items a wave of k_seed_left may take of them
+  bool sampled = false;     // sample_fn in place of the planner's scan
+  KernelFn sample_fn;
   Params prune_shape;       // the pr_ members only
 };
 mica_status_t plan_fills(int device, const uint8_t* class_of_m, const mica_batch_t* b, const mica_scoring_t* s,

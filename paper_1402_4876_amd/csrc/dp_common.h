@@ -103,6 +103,15 @@ constexpr uint32_t kSkip = 0xFFFFFFFFu;
 static_assert(kMaxM / kSeed < 256, "a part's number fits beside its bases");
 constexpr int kPruneParts = 2 * kNumModes;
 constexpr int kPruneItem = 8;          // pairs per item of the scan
+// Batches from this size on are sampled first (by so many waves, an item each),
+// for scores alone or of reads below this length: a traced table of longer ones
+// costs so much more than the scan that it pays for itself (100,000 of 150 x 400,
+// all unrelated: 2.7 ms of 4.3; 10% errors: 2.4 of 3.9).
+constexpr int kSamplePairs = 32768;
+constexpr int kSampleRead = 128;
+constexpr int kSampleWaves = 128;
+static_assert(kSampleWaves * kPruneItem == 1024, "the batch is n_pairs / 1024 samples");
+constexpr int kScanThreads = 256;      // one thread per bucket
 constexpr int kScanChunk = 8;          // items a wave of the scan takes, at most
 constexpr int kScanStaticWords = 192 + 4 * kPruneItem * kScanChunk;  // LDS words of a wave before its sequences (scan)
 constexpr int kBandStaticWords = 128;   // and before its band codes (band)
@@ -124,11 +133,10 @@ enum : int {
   kCtrPruneWide = kCtrSideHead + kPersistParts,  // pairs the band kernels finished or left to the full
   kCtrPruneMid,                                 // traceback, by band width: over 64 diagonals, 17-64
   kCtrPruneLeft,                                // pairs left to the full traceback
-  // four sums of 16 bits (64 bits, aligned): scanned pairs of the items that
-  // report; ones of them answered or listed; likely to hold; with a core
+  // per mode two 64-bit words of the sample: its pairs and, from bit 32, those that
+  // would be answered or listed for a band; the cells this would save
   kCtrSeed = (kCtrPruneLeft + 2) / 2 * 2,
-  kCtrSeedHigh,
-  kNumCounters
+  kNumCounters = kCtrSeed + 4 * kNumModes
 };
 
 // per-pair status bits (same values as the public header)
@@ -232,7 +240,9 @@ struct Params {
   uint32_t* rcount;            // [kNumBuckets] pairs left per bucket
   uint32_t* lcount;            // [kNumBuckets] pairs left to k_seed_left
   int32_t left_full_;          // pairs left go to the full traceback without a fill (see left_full)
-  int32_t left_waves;          // waves of its short-read launches (0: there are none)
+  int32_t left_limit;          // the items of short reads that k_seed_left takes
+  int32_t pr_sampled;          // the batch has been sampled
+  int32_t pr_sample_waves;     // waves a block that do so
   uint32_t* nbcount;           // [kNumBuckets] pairs on the band lists, of up to 16 diagonals
   uint32_t* w32count;          // [kNumBuckets] of 17-32
   uint32_t* w64count;          // [kNumBuckets] of 33-64
@@ -255,6 +265,8 @@ struct Params {
 // bases, whose band is narrow more often than not.
 __host__ __device__ inline bool left_full(const Params* p, int mode) { return p->left_full_ && mode != 2; }
 constexpr int kLeftFullRead = 100;
+// Reads below this are of few parts.
+constexpr int kFewPartsRead = 72;
 
 }  // namespace mica
 
@@ -269,7 +281,8 @@ struct KernelTable {
   KernelFn side[kNumBuckets];
   KernelFn side_persistent[kNumModes][2];
   KernelFn sidescan;
-  KernelFn seed_scan[2][2];             // [with traceback][32-bit]
+  KernelFn seed_sample[2][2];           // [with traceback][32-bit]
+  KernelFn seed_scan[2][2];
   KernelFn seed_band[2][2][kNumModes];  // [with traceback][32-bit][mode]
   KernelFn seed_left[2][kNumModes][2];  // [32-bit][mode][long reads]
   KernelFn rescan;                      // after them

@@ -310,10 +310,16 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   // that finds the reads too noisy costs some 50 us (70,000 of 60 x 120, 6%
   // errors: 261 us without it, 304 with it; 140,000 of 150 x 300: 1.20, 1.26 ms).
   if (!traced && (b->n_pairs < 65536 || (double)b->n_pairs * b->max_read_len * b->max_win_len < 3e9)) return MICA_OK;
-  // two parts at least to hope for an answer (local: three), four where that
-  // saves no traceback
+  // four parts at least: 20,000 traced pairs of 30 x 109 take 157 us here and 176
+  // in the fills without errors, 262 and 185 with 5%
   const int parts = b->max_read_len / kSeed;
-  if (!any_mode[MICA_MODE_EXTEND] && parts < (traced ? (any_mode[MICA_MODE_SEMIGLOBAL] ? 2 : 3) : 4)) return MICA_OK;
+  if (!any_mode[MICA_MODE_EXTEND] && parts < 4) return MICA_OK;
+  // Traced reads of few parts are often left, and a fill of some thousands of them
+  // is as quick as one of those left (60 x 154 local, 20,000: 257 us without
+  // errors, 278 with 5%; here 197 and 385; 40,000: 346 and 378; here 228 and 424).
+  if (traced && !any_mode[MICA_MODE_EXTEND] && b->max_read_len < kFewPartsRead && b->n_pairs >= 4096 &&
+      b->n_pairs < 32768)
+    return MICA_OK;
   // (the pairs left run in up to 256 dummy rows, more than the planner's 16-bit
   // check of short reads allows for)
   if (!(flags & MICA_FORCE_INT32) && 2L * s.gap_open + (long)(kMaxM + 1) * s.gap_extend + 256 > 32767 - 8) return MICA_OK;
@@ -346,6 +352,8 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   block(S.pr_band_words, &fp->prune_threads, &fp->prune_shmem);
   const int wide = (flags & MICA_FORCE_INT32) ? 1 : 0;
   fp->scan_fn = kernels().seed_scan[traced][wide];
+  fp->sample_fn = kernels().seed_sample[traced][wide];
+  fp->sampled = b->n_pairs >= kSamplePairs && (!traced || m < kSampleRead);
   int n_prune = 0;
   for (int md = 0; md < kNumModes; ++md) {
     if (!any_mode[md]) continue;
@@ -359,6 +367,15 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   S.left_full_ = traced && m > kLeftFullRead ? 1 : 0;
   fp->n_left = 0;
   fp->left_pairs = wide ? 1 : 2;
+  // (their items have 128 rows at least, whatever the reads: 9,000 items of 60
+  // bases take 250 us there, 221 in a fill and its side lists)
+  fp->left_rounds = m <= 64 && (any_mode[MICA_MODE_SEMIGLOBAL] || any_mode[MICA_MODE_LOCAL]) ? 2 : 4;
+  bool short_class[kNumClasses] = {};
+  for (int r = std::max(1, b->min_read_len); r <= m; ++r) short_class[class_of_m[r]] = !left_long(class_of_m[r]);
+  fp->left_buckets = 0;
+  for (int c = 0; c < kNumClasses; ++c) {
+    for (int md = 0; md < kNumModes; ++md) fp->left_buckets += short_class[c] && any_mode[md] ? 1 : 0;
+  }
   for (int md = 0; md < kNumModes && traced; ++md)
     for (int lng = 0; lng < 2; ++lng) {
       bool used = false;
@@ -388,9 +405,8 @@ int64_t prune_slots(const FillPlan& fp, int n_cu, int64_t n_pairs, size_t bytes)
   return std::min(slots, (int64_t)(bytes / fp.prune_shape.pr_slot_bytes) / per_block * per_block);
 }
 
-// Items a wave of the scan takes: about two waves per SIMD, so that what the
-// first items of a batch of unrelated pairs gave spares it the others, and at
-// least one list request per kScanChunk items.
+// Items a wave of the scan takes: about two waves per SIMD, and at most one list
+// request per kScanChunk items.
 static int scan_chunk(int n_cu, int64_t n_pairs) {
   const int64_t per_wave = n_pairs / kPruneItem / ((int64_t)n_cu * 8);
   return (int)std::max<int64_t>(1, std::min<int64_t>(kScanChunk, per_wave));
@@ -414,7 +430,9 @@ static int64_t left_short_waves(const FillPlan& fp, int n_cu, int64_t n_pairs, i
 void prune_params(Params* P, const FillPlan& fp, int n_cu, int64_t slots, int64_t fill_slots, uint32_t* rerun,
                   uint32_t* wlist, uint32_t* small) {
   P->lcount = small + small::kLcount;
-  P->left_waves = (int32_t)left_short_waves(fp, n_cu, P->n_pairs, fill_slots);
+  P->left_limit = (int32_t)(fp.left_rounds * left_short_waves(fp, n_cu, P->n_pairs, fill_slots));
+  P->pr_sampled = fp.sampled ? 1 : 0;
+  P->pr_sample_waves = fp.scan_threads / 64;
   P->pr_chunk = scan_chunk(n_cu, P->n_pairs);
   const Params& S = fp.prune_shape;
   P->presorted = rerun;
@@ -449,7 +467,10 @@ void launch_sequence(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t slot
     const unsigned blocks = (unsigned)((n_pairs + kPlanPairsPerBlock - 1) / kPlanPairsPerBlock);
     seq->push_back({K.zero, 1, 256, 0, false});
     seq->push_back({K.plan, blocks, kPlanThreads, 0, false});
-    seq->push_back({K.scan, 1, 256, 0, false});
+    if (pr_slots > 0 && fp.sampled)
+      seq->push_back({fp.sample_fn, 1 + (unsigned)(kSampleWaves * 64 / fp.scan_threads), kScanThreads, fp.scan_shmem, false});
+    else
+      seq->push_back({K.scan, 1, kScanThreads, 0, false});
     seq->push_back({K.scatter, blocks, kPlanThreads, 0, false});
   }
   if (pr_slots > 0) {
@@ -468,8 +489,10 @@ void launch_sequence(const FillPlan& fp, int n_cu, int64_t n_pairs, int64_t slot
   bool lw_all = false;
   if (pr_slots > 0) {
     // (can the short reads' launches take whatever is left?)
-    const int64_t lw = left_short_waves(fp, n_cu, n_pairs, slots);
-    lw_all = 4 * lw >= n_pairs / fp.left_pairs + kNumModes * kNumClasses;
+    const uint64_t lw = (uint64_t)left_short_waves(fp, n_cu, n_pairs, slots);
+    const uint64_t per = (uint64_t)fp.left_pairs, n = (uint64_t)n_pairs;
+    const uint64_t most = std::min(n, (n + (per - 1) * (uint64_t)fp.left_buckets) / per);
+    lw_all = most <= fp.left_rounds * lw;
     for (int i = 0; i < fp.n_left; ++i) {
       const int64_t waves = left_waves(fp, i, n_cu, n_pairs, slots);
       seq->push_back({fp.left[i], (unsigned)(waves / kWavesPerBlock), 256, kFillShmem, true});

@@ -36,7 +36,8 @@
 // band, with a loss the parts cannot certify or with two equal parts is left
 // to the fills, unchanged.
 //
-// Three kernels.  k_seed_scan: a wave scans 8 pairs, answers those without a
+// Four kernels.  k_seed_sample: in large batches for which looking may not pay,
+// whether it does.  k_seed_scan: a wave scans 8 pairs, answers those without a
 // gap, and lists the others with their band; it needs few registers, so many
 // waves hide its chain of dependent loads.  k_seed_band: the listed bands, 8
 // pairs (4 in 32 bits) to a wave, the wide ones first; a band that turns out
@@ -52,15 +53,16 @@
 #pragma once
 
 #include "dp_fill.h"
+#include "plan_scan.h"
 
 namespace mica {
 
 // Resident waves per SIMD.
 constexpr int kScanWaves = 6;
-// waves that may report on their first item (the sums fit 16 bits)
-constexpr uint32_t kSeedReporters = 65536;
-static_assert(kSeedReporters / 16 * kPruneItem < 65536, "sums of 16 bits");
-__host__ __device__ constexpr int band_waves(int kind, int mode, bool trace) { return 4; }
+// pairs that keep the GPU busy for more than an item's time
+constexpr int kBusyPairs = 16384;
+constexpr int kDearWindow = 768;
+constexpr int kBandWaves = 4;
 
 // The scan's LDS words of a pair before its window and read: {lowest, highest
 // diagonal, occurrences, -, parts that occur (3 words), -}, the diagonals of
@@ -186,25 +188,17 @@ __device__ __forceinline__ void write_out(const Params* __restrict__ prm, int mo
   else if (mode == 1) write_out<1, TRACE>(prm, bucket, lds, cnt, b);
   else write_out<2, TRACE>(prm, bucket, lds, cnt, b);
 }
-// All the wave listed goes to list 0, the pairs left.
-__device__ __forceinline__ void all_left(uint32_t* lds, int cnt[4]) {
-  const int lane = threadIdx.x & 63;
-  uint32_t* out = lds + kPrOutOff;
-  lds_wait();
-  for (int li = 1; li < 4; ++li) {
-    if (lane < cnt[li]) out[cnt[0] + lane] = out[li * kPrOut + lane];
-    cnt[0] += cnt[li];
-    cnt[li] = 0;
-  }
-  lds_wait();
-}
-
-// The scan of an item of up to 8 pairs (8 lanes each) of one bucket; how many
-// of them it answered or listed for a band, how many of those are likely to
-// hold (bits 8 up) and how many had a core at all (bits 16 up).
-template <class V, int MODE, bool TRACE>
-__device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const uint32_t* pairs, int np, int bucket,
-                                          uint32_t* lds, int* cnt, BandCount* count) {
+// The scan of an item of up to 8 pairs of one mode, pair p of 8 lanes where
+// they are valid.  SAMPLE: only how many of them it would answer or list for a
+// band, and the table cells this saves less its own cost (saved).  10^6 pairs of
+// 150 x 400 take 10.7 ms in the fill, 0.18 us per 1,000 cells; a pair's scan as
+// long as 1,400 cells and 5% of the table, a row of a band of 16 diagonals as
+// long as 112 columns (scores alone 90), of 32 and 64 two and four times that.
+// A traced pair refills its band, some 64 columns, and may pass through a side
+// list, a tenth of the time more (local, whose cells are dearer too, half).
+template <class V, int MODE, bool TRACE, bool SAMPLE>
+__device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, bool valid, int p, uint32_t* lds, int* cnt,
+                                          BandCount* count, int* saved = nullptr) {
   constexpr bool EXT = (MODE == 2);
   constexpr bool LOCAL = (MODE == 1);
   const int lane = threadIdx.x & 63;
@@ -219,11 +213,9 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
   int* const res = (int*)lds + q * kPrPair;
   int* const hit = res + 8;
 
-  const bool valid = q < np;
-  int p = 0, m = 0, n = 0, h0 = 0;
+  int m = 0, n = 0, h0 = 0;
   uint64_t wo = 0, ro = 0;
   if (valid) {
-    p = (int)G(pairs)[q];
     m = G(prm->read_len)[p];
     n = G(prm->win_len)[p];
     wo = G(prm->win_off)[p];
@@ -306,7 +298,8 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
         });
       }
       if (__ballot(any) == 0) {  // none of these pairs
-        put_out(lds, 0, &cnt[0], valid && x == 0, (uint32_t)p);
+        if constexpr (SAMPLE) *saved = 0;
+        else put_out(lds, 0, &cnt[0], valid && x == 0, (uint32_t)p);
         lds_wait();
         return 0;
       }
@@ -367,6 +360,7 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
   const bool one = ok && (EXT ? n >= m : (core.span == 0 && c0 >= 0 && c0 + m <= n));
   const bool look = ok && (EXT || one);
   int mism = 0, best = h0;  // best (extension): the best prefix of diagonal 0
+  int total = 0, dense = 0;  // all mismatches, and those of words full of them
   lds_wait();
   {
     const int len = EXT ? nl : m;
@@ -374,19 +368,22 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
     for (int r = 0; r < rounds; ++r) {
       const int w = x + 8 * r;
       uint32_t d = 0;
+      int bases = 0;
       if (look && 16 * w < len) {
         const uint32_t v = rd[q * RN + w] ^ lds_bases(win + q * WN, c0 + 16 * w);
         d = (v | (v >> 1)) & 0x55555555u;
-        if (len - 16 * w < 16) d &= (1u << (2 * (len - 16 * w))) - 1u;
+        bases = len - 16 * w;
+        if (bases < 16) d &= (1u << (2 * bases)) - 1u;
       }
       const int c = __builtin_popcount(d);
-      int incl = c;
+      const bool full = !EXT && (c > 4 || 2 * c > bases);
+      int incl = full ? c * 0x10001 : c;
 #pragma unroll
       for (int s = 1; s < 8; s <<= 1) {
         const int o = __shfl_up(incl, s, 8);
         if (x >= s) incl += o;
       }
-      int k = mism + incl - c;
+      int k = mism + (incl & 0xFFFF) - c;
       if constexpr (EXT) {
         if (look && 16 * w < len) {
           const int v = h0 + sa * (len < 16 * w + 16 ? len : 16 * w + 16) - (sa - sb) * (k + c);
@@ -409,7 +406,12 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
         if (k < kPrHits) hit[k] = at;
         ++k;
       }
-      mism += __shfl(incl, 7, 8) + (many ? kPrHits + 1 : 0);
+      const int sum = __shfl(incl, 7, 8);
+      mism += (sum & 0xFFFF) + (many ? kPrHits + 1 : 0);
+      if constexpr (!EXT) {
+        total += sum & 0xFFFF;
+        dense += sum >> 16;
+      }
     }
     if constexpr (EXT) best = max8(best);
   }
@@ -417,8 +419,12 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
 
   // ---- no gap possible: the diagonal is the answer ----------------------------
   const int gap = so + se;  // the least loss of a gap
+  // whether a band that fails costs more than it might save: not where a table is
+  // several bands' worth, nor in a batch of one item's time
+  const bool busy = prm->n_pairs >= kBusyPairs && n < kDearWindow;
+  const bool known = !EXT && one && mism <= kPrHits;  // every mismatch's place
   bool direct = false;
-  int score = 0, ie = 0, i0 = 0;
+  int score = 0, ie = 0, i0 = 0, crowd = 0;
   if constexpr (EXT) {
     // no parts were searched: with one mismatch at most, every gapped
     // alignment scores less than both of the diagonal's ends
@@ -437,7 +443,7 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
     bool leaves = false;  // leaving the diagonal might pay
     const int lose2 = 2 * (sa - sb);
     const int cx2 = LOCAL ? prm->pr_costs.leave2_local : prm->pr_costs.leave2;
-    const int few = one && mism <= kPrHits ? mism : 0;
+    const int few = known ? mism : 0;
     auto saved2 = [&](int from, int to, int k, int free) -> int {
       return leave_saves2(lose2, cx2, T, from, to, k, free);
     };
@@ -452,7 +458,13 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
       for (int j = i; j < few; ++j) leaves |= saved2(pi, hit[j], j - i + 1, 2) >= 4 * gap;
     }
     leaves = (__ballot(leaves) >> (8 * q) & 0xFFu) != 0;
-    if (one && mism <= kPrHits && !leaves) {
+    if (busy) {
+      int at = 0;  // mismatches of the first and (from bit 16) of the last part
+      for (int i = x; i < few; i += 8) at += (hit[i] < kSeed ? 1 : 0) + (hit[i] >= m - kSeed ? 0x10000 : 0);
+      at = sum8(at);
+      crowd = (at & 0xFFFF) > (at >> 16) ? at & 0xFFFF : at >> 16;
+    }
+    if (known && (busy || !leaves)) {
       if constexpr (LOCAL) {
         // the best stretch of the diagonal: H along it, back to 0 where it
         // would not stay above (the traceback stops at the last 0)
@@ -476,12 +488,12 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
         score = sa * m - (sa - sb) * mism;
         ie = m;
       }
-      direct = loss_certain(prm->pr_costs, LOCAL, T, sa * m - score);
+      direct = !leaves && loss_certain(prm->pr_costs, LOCAL, T, sa * m - score);
     }
   }
   // (ie = 0: the anchor itself, or a local read that matches nowhere)
   direct = direct && ie > 0;
-  if (direct && x == 0) {
+  if (!SAMPLE && direct && x == 0) {
     const int je = ie + c0;
     G(prm->score)[p] = score;
     G(prm->read_end)[p] = ie;
@@ -517,41 +529,148 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, const 
       ns = (hi - lo + 16) >> 4;
       margin = kProven;
     } else {
-      // the loss to expect: parts without an occurrence stand for
-      // substitutions, two diagonals (or a tail full of mismatches) for a gap
-      // (scores alone: u of T parts hit at random hold some u + u u / 2 T)
-      auto subs = [&](int u) -> int { return (sa - sb) * (TRACE ? u : u + u * u / (2 * T)); };
-      int loss = subs(missed);
+      // the loss to expect.  Of an alignment along the one diagonal, its own,
+      // which bounds the best one's, so a band for it is certain to hold; a gap
+      // (a word full of mismatches) may lose less.  Else u of T parts without an
+      // occurrence hold T ln(T / (T - u)) substitutions where they fall at
+      // random.  (With one for each part, 70% of reads of 100 bases with 10%
+      // errors went to a band, three quarters of them for nothing: 100,000 in
+      // windows of 214: 705 us of bands in place of 194.)  Where a band that fails
+      // is cheap beside a pair left, one substitution a part is hoped for.
+      auto subs = [&](int u) -> int {
+        if (u < 1) return 0;
+        if (!busy) return (sa - sb) * u;
+        const float f = (float)u * __builtin_amdgcn_rcpf((float)T);
+        return (sa - sb) * (int)((float)u * (1.0f + f * (0.5f + f * 0.3333f)));
+      };
+      int loss;
+      bool sure = false;  // an alignment of this loss is known
       if (core.span > 0) {
-        loss = so + (se + sa) * (core.span < 4 ? core.span : 4) + subs(missed > 1 ? missed - 1 : 0);
-      } else if (!one || mism > missed + 1) {
-        loss += so + 2 * se;
+        loss = so + (se + sa) * (core.span < 4 ? core.span : 4) + subs(missed - 1);
+      } else if (one) {
+        loss = score > 0 ? sa * m - score : (sa - sb) * total;
+        sure = true;
+        // (or one next to an end: three mismatches of its last bases)
+        int other = crowd >= 3 ? so + 2 * se + (sa - sb) * (total - crowd) : loss;
+        if (dense > 0) {
+          const int gap = so + 2 * se + (sa - sb) * (total - dense + 1);
+          other = gap < other ? gap : other;
+          if constexpr (LOCAL) {  // (or clipped)
+            const int clip = 2 * sa * dense + (sa - sb) * (total - dense);
+            other = clip < other ? clip : other;
+          }
+        }
+        if (!busy) {
+          const int hope = subs(missed) + (mism > missed + 1 ? so + 2 * se : 0);
+          other = hope < other ? hope : other;
+        }
+        if (other < loss) {
+          loss = other;
+          sure = false;
+        }
+      } else {
+        loss = so + 2 * se + subs(busy ? missed - 1 : missed);
       }
       ns = 99;
       // (scores alone: a band that fails costs more than it may save, and over 32
       // diagonals nearly as much as the table)
-      if (loss_certain(prm->pr_costs, LOCAL, T, TRACE ? loss : loss + loss / 4))
+      if (loss_certain(prm->pr_costs, LOCAL, T, TRACE || sure ? loss : loss + loss / 4))
         ns = band_strips(core.span, loss_drift(prm->pr_costs, core, loss));
       if (!TRACE && ns > 2) ns = 99;
       margin = ns <= 4 ? band_margin(core.span, ns) : 0;
       lo = c0 - margin;
     }
   }
+  // (a band's cell costs some four of the table's, whose traced pairs refill 16
+  // diagonals besides: wide bands of short extensions cost more than their tables)
+  if (EXT && busy && (ns > 2 ? 512 : 256) > 3 * (n + (TRACE ? 64 : 0))) ns = 99;
   const bool go = ok && !direct && ns <= 4;
-  if (go && x == 0) {
-    G(prm->bucket_of)[p] = band_word(lo, margin, ns > 1 ? ns : 1);
-    G(prm->dbsorted)[p] = core_word(core);
+  if constexpr (!SAMPLE) {
+    if (go && x == 0) {
+      G(prm->bucket_of)[p] = band_word(lo, margin, ns > 1 ? ns : 1);
+      G(prm->dbsorted)[p] = core_word(core);
+    }
+    put_out(lds, 0, &cnt[0], valid && x == 0 && !direct && !go, (uint32_t)p);
+    put_out(lds, 1, &cnt[1], x == 0 && go && ns <= 1, (uint32_t)p);
+    put_out(lds, 2, &cnt[2], x == 0 && go && ns == 2, (uint32_t)p);
+    put_out(lds, 3, &cnt[3], x == 0 && go && ns > 2, (uint32_t)p);
   }
-  put_out(lds, 0, &cnt[0], valid && x == 0 && !direct && !go, (uint32_t)p);
-  put_out(lds, 1, &cnt[1], x == 0 && go && ns <= 1, (uint32_t)p);
-  put_out(lds, 2, &cnt[2], x == 0 && go && ns == 2, (uint32_t)p);
-  put_out(lds, 3, &cnt[3], x == 0 && go && ns > 2, (uint32_t)p);
   lds_wait();
-  // (of reads that lost more than a third of their parts few bands hold;
-  // extensions know their band from the loss itself)
-  const bool likely = direct || (EXT ? ok : go && 3 * missed <= T);
-  return __builtin_popcountll(__ballot(x == 0 && (direct || go))) | __builtin_popcountll(__ballot(x == 0 && likely)) << 8 |
-         __builtin_popcountll(__ballot(x == 0 && ok)) << 16;
+  if constexpr (SAMPLE) {
+    int v = 0;
+    if (valid && x == 0) {
+      v = -(1400 + m * n / 20);
+      if (direct || go) v += TRACE ? m * (n + 64) / 10 * (LOCAL ? 15 : 11) : m * n;
+      if (go) v -= m * (TRACE ? 112 : 90) * (ns > 2 ? 4 : (ns > 1 ? 2 : 1));
+    }
+#pragma unroll
+    for (int s = 8; s < 64; s <<= 1) v += __shfl_xor(v, s, 64);
+    *saved = v;  // of lane 0
+  }
+  return __builtin_popcountll(__ballot(x == 0 && (direct || go)));
+}
+
+// Block 0: the planner's scan.  The others look at a sample of the batch,
+// kSampleWaves items of 8 pairs spread over it, so that the scan below is spared
+// a batch without hope: what it finds of unrelated pairs, or of reads with too
+// many errors for a certificate, does not pay for its looking (100,000 local
+// reads of 60 in windows of 154, 5% errors, traced: 761 us with the scan, 677
+// without).  An item's time (10-20 us) in place of the 5 of block 0 alone.
+template <class V, bool TRACE>
+__global__ __launch_bounds__(kScanThreads) void k_seed_sample(const Params* __restrict__ prm) {
+  constexpr int KIND = V::kPairs == 1 ? kK32 : kK16;
+  extern __shared__ uint32_t smem[];
+  static_assert(kScanTableWords <= kScanStaticWords, "the scan's tables fit a wave's LDS");
+  if (blockIdx.x == 0) {
+    scan_tables(prm, smem);
+    return;
+  }
+  const int wave = uni((int)(threadIdx.x >> 6));
+  if (wave >= prm->pr_sample_waves) return;
+  const uint32_t w = (blockIdx.x - 1) * (uint32_t)prm->pr_sample_waves + (uint32_t)wave;
+  const int q = (int)(threadIdx.x & 63) >> 3;
+  const uint64_t at = (uint64_t)(w * kPruneItem + (uint32_t)q) * (uint64_t)prm->n_pairs / (kSampleWaves * kPruneItem);
+  const int p = (int)at;
+  const uint32_t b = G(prm->bucket_of)[p];
+  const bool in = b != kSkip && bucket_kind((int)(b / kSubBins)) == KIND;
+  const int md = in ? bucket_mode((int)(b / kSubBins)) : -1;
+  uint32_t* lds = smem + wave * prm->pr_scan_words;
+  BandCount count{0, 0};
+  auto look = [&](auto mode) {
+    constexpr int MODE = decltype(mode)::value;
+    const uint64_t some = __ballot(md == MODE);
+    if (some == 0) return;
+    int saved = 0;
+    const int got = prune_scan<V, MODE, TRACE, true>(prm, md == MODE, p, lds, nullptr, &count, &saved);
+    if ((threadIdx.x & 63) == 0) {
+      unsigned long long* const sum = (unsigned long long*)(prm->counters + kCtrSeed) + 2 * MODE;
+      atomicAdd(sum, (unsigned long long)(__builtin_popcountll(some) >> 3) | (unsigned long long)got << 32);
+      atomicAdd(sum + 1, (unsigned long long)(long long)saved);
+    }
+  };
+  look(std::integral_constant<int, 0>{});
+  look(std::integral_constant<int, 1>{});
+  look(std::integral_constant<int, 2>{});
+}
+
+// Whether the sample says to leave a mode's pairs.  Beyond what k_seed_left
+// takes in two rounds (three where few are left), the pairs left go through the
+// fills and their side lists, whose time hardly falls below that of one round of items (300 us of 454
+// for 100,000 traced pairs of 50 x 139, a quarter of which were left), so the
+// saving has to be more than that: the lines that part 60 batches of 40,000 to
+// 300,000 pairs best (most of those on the wrong side lose under 4%; 0.85 to
+// 0.95 of the full tables' speed without them).
+__host__ __device__ constexpr long long saved_cells(bool trace) { return trace ? 2000000000 : 1000000000; }
+template <bool TRACE>
+__device__ __forceinline__ bool hopeless(const Params* __restrict__ prm, int mode, int per) {
+  const unsigned long long* const sum = (const unsigned long long*)(prm->counters + kCtrSeed) + 2 * mode;
+  const uint32_t tried = (uint32_t)sum[0], found = (uint32_t)(sum[0] >> 32);
+  const long long share = prm->n_pairs >> 10;
+  if (8u * found < tried) return true;
+  if (mode == 2 || tried == 0) return false;
+  const long long left = (tried - found) * share, limit = (long long)per * prm->left_limit;
+  if (TRACE && (2 * left <= limit || (4 * left <= 3 * limit && 4 * (tried - found) <= tried))) return false;
+  return (long long)sum[1] * share < saved_cells(TRACE);
 }
 
 // The scan of every pair of the batch, pr_chunk items of 8 pairs per wave:
@@ -575,35 +694,14 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
   const uint32_t starts = in ? qs[lane / kNumClasses * (kNumClasses + 1) + lane % kNumClasses] : 0xFFFFFFFFu;
   uint32_t* lds = smem + wave * prm->pr_scan_words;
 
-  // A batch of unrelated pairs would pay for scans that find nothing: one wave
-  // in 16 reports what its first item gave, and while that is less than one
-  // pair in eight, seven of eight items pass unseen.  (Read by a block at its
-  // start and by a wave after an item that gave little: every read goes past
-  // the L2.)
-  // Where a band saves less, for scores alone and for short reads, the others
-  // pass unseen altogether, and the batch is also left if most of the reads
-  // with a core hold too many errors (70,000 local reads of 60 x 120, 6%
-  // errors: 0.74 ms with their bands, 0.61 without; 2%: 0.38 and 0.41).
   __shared__ int head[kWavesPerBlock][9];  // bucket, four counts, four list positions of each wave
-  __shared__ bool rare_at[2];  // the block's look at its start and at its end
-  const bool cut = !TRACE || prm->pr_rows < 96;
-  unsigned long long* const seen = (unsigned long long*)(prm->counters + kCtrSeed);
-  auto look = [&]() -> bool {
-    const uint64_t v = __hip_atomic_load(seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t tried = (uint32_t)v & 0xFFFFu, found = (uint32_t)v >> 16;
-    const uint32_t likely = (uint32_t)(v >> 32) & 0xFFFFu, cores = (uint32_t)(v >> 48);
-    return tried >= 64u && (8u * found < tried || (cut && 2u * likely < cores));
-  };
-  const bool reporter = (w & 15u) == 0 && w < kSeedReporters;
-  if (threadIdx.x == 0) rare_at[0] = look();
-  __syncthreads();
-  bool ask = false, rare = rare_at[0];
+  uint32_t leave = 0;                      // modes whose pairs pass unseen
+  if (prm->pr_sampled)
+    for (int md = 0; md < kNumModes; ++md) leave |= hopeless<TRACE>(prm, md, V::kPairs) ? 1u << md : 0u;
   BandCount count{0, 0};
   int cnt[4] = {0, 0, 0, 0};
   int mode = 0, bucket = -1;
   for (; it < end; ++it) {
-    if (ask && !(cut && rare)) rare = look();
-    ask = false;
     const int pos = __builtin_popcountll(__ballot(in && starts <= it)) - 1;
     const int md = pos / kNumClasses;
     const int b = bucket_id(KIND, prune_class(pos - md * kNumClasses), md);
@@ -627,35 +725,28 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
     const uint32_t left = G(prm->bcount)[b] - first;
     const uint32_t* pairs = prm->presorted + G(prm->bstart)[b] + first;
     const int np = left < (uint32_t)kPruneItem ? (int)left : kPruneItem;
-    const bool report = reporter && it % chunk == 0;
-    if (rare && (cut ? !report : (it & 7u) != 0)) {
+    if ((leave >> md) & 1u) {
       uint32_t p = 0;
       if (lane < np) p = G(pairs)[lane];
       put_out(lds, 0, &cnt[0], lane < np, p);
     } else {
-      int got;
-      if (md == 0) got = prune_scan<V, 0, TRACE>(prm, pairs, np, b, lds, cnt, &count);
-      else if (md == 1) got = prune_scan<V, 1, TRACE>(prm, pairs, np, b, lds, cnt, &count);
-      else got = prune_scan<V, 2, TRACE>(prm, pairs, np, b, lds, cnt, &count);
-      const int found = got & 0xFF, likely = got >> 8 & 0xFF, cores = got >> 16;
-      ask = found == 0 || (cut && 2 * likely < cores);
-      if (report && lane == 0)
-        atomicAdd(seen, (unsigned long long)np | (unsigned long long)found << 16 | (unsigned long long)likely << 32 |
-                            (unsigned long long)cores << 48);
+      const bool valid = (lane >> 3) < np;
+      const int p = valid ? (int)G(pairs)[lane >> 3] : 0;
+      if (md == 0) prune_scan<V, 0, TRACE, false>(prm, valid, p, lds, cnt, &count);
+      else if (md == 1) prune_scan<V, 1, TRACE, false>(prm, valid, p, lds, cnt, &count);
+      else prune_scan<V, 2, TRACE, false>(prm, valid, p, lds, cnt, &count);
     }
   }
 
   // The block's waves ask for room together: the counts of a bucket serve
   // about one request in 12 ns, and a request per wave and list keeps them
   // busy for 75 us in 400,000 pairs.
-  if (cut && threadIdx.x == 0) rare_at[1] = rare || look();
   if (lane == 0) {
     head[wave][0] = bucket;
 #pragma unroll
     for (int li = 0; li < 4; ++li) head[wave][1 + li] = cnt[li];
   }
   __syncthreads();
-  const bool noisy = cut && rare_at[1];
   int lead = wave;
   uint32_t at[4] = {0, 0, 0, 0};
   if (bucket >= 0) {
@@ -664,7 +755,6 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
       if (head[v][0] != bucket) continue;
       uint32_t c = 0;
       if (lane < 4) c = (uint32_t)head[v][1 + lane];
-      if (noisy) c = lane == 0 ? (uint32_t)(head[v][1] + head[v][2] + head[v][3] + head[v][4]) : 0u;
       sum += c;
       if (v < wave) before += c;
       lead = v < lead ? v : lead;
@@ -672,7 +762,6 @@ __global__ __launch_bounds__(256, kScanWaves) void k_seed_scan(const Params* __r
     if (lead == wave && lane < 4) head[wave][5 + lane] = sum ? (int)atomicAdd(out_count(prm, lane, bucket), sum) : 0;
 #pragma unroll
     for (int li = 0; li < 4; ++li) at[li] = (uint32_t)__builtin_amdgcn_readlane((int)before, li);
-    if (noisy) all_left(lds, cnt);
   }
   __syncthreads();
   if (bucket >= 0) {
@@ -1053,8 +1142,7 @@ __global__ __launch_bounds__(256, LONG ? 2 : 4) void k_seed_left(const Params* _
 // The bands of a mode, the wide ones first, in items of a wave's worth of
 // pairs of one bucket.
 template <class V, int MODE, bool TRACE>
-__global__ __launch_bounds__(256, band_waves(V::kPairs == 1 ? kK32 : kK16, MODE, TRACE)) void
-k_seed_band(const Params* __restrict__ prm) {
+__global__ __launch_bounds__(256, kBandWaves) void k_seed_band(const Params* __restrict__ prm) {
   constexpr int KIND = V::kPairs == 1 ? kK32 : kK16;
   constexpr int PART = prune_part(KIND, MODE);
   constexpr int P16 = 4 * V::kPairs, P32 = 2 * V::kPairs, P64 = V::kPairs;  // pairs per item

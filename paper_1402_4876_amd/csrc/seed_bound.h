@@ -39,6 +39,8 @@ struct SeedCosts {
   int cost2, cost2_local;
   int leave2, leave2_local;
   int move2_del, move2_ins;
+  // 2^32 over twice e, a + e and a + 2 e, rounded up
+  uint32_t per_del, per_ins, per_both;
 };
 
 // Twice the least loss per spoiled part: a substitution or a deletion spoils
@@ -71,6 +73,10 @@ inline SeedCosts seed_costs(int a, int b, int o, int e, int max_parts) {
   const int move2 = least(c.leave2, 2 * kSeed * a);
   c.move2_del = least(move2, 2 * o);
   c.move2_ins = least(move2, o);
+  auto over = [](int per) { return (uint32_t)(((1ull << 32) + 2 * (uint64_t)per - 1) / (2 * (uint64_t)per)); };
+  c.per_del = over(e);
+  c.per_ins = over(a + e);
+  c.per_both = over(a + 2 * e);
   return c;
 }
 
@@ -97,20 +103,24 @@ __host__ __device__ __forceinline__ bool loss_certain(const SeedCosts& c, bool l
 // The parts that w inserted bases swallow past the two that each run touches.
 __host__ __device__ __forceinline__ int swallowed(int w) { return w > 2 ? (w - 2) / kSeed : 0; }
 
-// The most inserted bases, `per` a base, that a doubled loss left2 allows
-// beside `parts` parts of cost2 each, of which the bases swallow some.  (Not
-// monotone: a base that completes a part may pay for itself.  Every allowed
-// number is at most what the parts it leaves allow, so it stays at most w as w
-// falls from what no part at all allows to the largest number that holds.)
-__host__ __device__ __forceinline__ int inserted_bases(int left2, int per, int parts, int cost2) {
-  auto len = [&](int charged) -> int {
-    const int l = left2 - (charged > 0 ? charged * cost2 : 0);
-    return l >= 2 * per ? (int)((uint32_t)l / (uint32_t)(2 * per)) : 0;
-  };
-  int w = len(0), k;
+// The bases that a doubled loss left2 pays for, 2^32 / per their doubled price
+// rounded up (so the quotient is never too low; a division takes some 20
+// instructions).
+__host__ __device__ __forceinline__ int paid_bases(int left2, uint32_t per) {
+  return left2 > 0 ? (int)(((uint64_t)(uint32_t)left2 * per) >> 32) : 0;
+}
+
+// The most inserted bases that left2 pays for beside `parts` parts of cost2
+// each, of which the bases swallow some.  (Not monotone: a base that completes a
+// part may pay for itself.  Every allowed number is at most what the parts it
+// leaves allow, so it stays at most w as w falls from what no part at all allows
+// to the largest number that holds.)
+__host__ __device__ __forceinline__ int inserted_bases(int left2, uint32_t per, int parts, int cost2) {
+  int w = paid_bases(left2, per), k;
+  if (parts <= 0) return w;
   do {
     k = swallowed(w);
-    w = len(parts - k);
+    w = paid_bases(left2 - (parts > k ? (parts - k) * cost2 : 0), per);
   } while (swallowed(w) != k);
   return w;
 }
@@ -140,23 +150,20 @@ __host__ __device__ __forceinline__ int inserted_bases(int left2, int per, int p
 __host__ __device__ __forceinline__ int loss_drift(const SeedCosts& c, const Core& k, int loss) {
   const int a = c.a, e = c.ext, cd = c.move2_del, ci = c.move2_ins;
   auto rest = [](int parts, int per) { return parts > 0 ? parts * per : 0; };
-  auto bases = [](int left2, int per) -> int {
-    return left2 >= 2 * per ? (int)((uint32_t)left2 / (uint32_t)(2 * per)) : 0;
-  };
   const int l2 = 2 * (loss - c.open);
   const int parts = k.missed + k.hmin;
-  int w = bases(l2 - rest(parts - 1, cd), e);
-  int v = inserted_bases(l2, a + e, parts - 2, ci);
+  int w = paid_bases(l2 - rest(parts - 1, cd), c.per_del);
+  int v = inserted_bases(l2, c.per_ins, parts - 2, ci);
   w = v > w ? v : w;
   if (k.hmin > 0) {
     const int s = k.span, d2 = l2 - 2 * (c.open + s * e);
-    v = bases(d2 - rest(k.missed - 2, cd), e);
+    v = paid_bases(d2 - rest(k.missed - 2, cd), c.per_del);
     w = v > w ? v : w;
-    v = inserted_bases(d2, a + 2 * e, k.missed - 3, ci);
+    v = inserted_bases(d2, c.per_both, k.missed - 3, ci);
     w = v > w ? v : w;
-    v = bases(d2 - 2 * s * (a + e) - rest(k.missed - 3 - (s + kSeed - 3) / kSeed, ci), e);
+    v = paid_bases(d2 - 2 * s * (a + e) - rest(k.missed - 3 - (s + kSeed - 3) / kSeed, ci), c.per_del);
     w = v > w ? v : w;
-    v = inserted_bases(l2 - 2 * c.open, a + e, k.missed - 4, ci) - s;
+    v = inserted_bases(l2 - 2 * c.open, c.per_ins, k.missed - 4, ci) - s;
     w = v > w ? v : w;
   }
   return w;
