@@ -24,6 +24,7 @@ mica_status_t fail(mica_status_t st, const std::string& msg);
   } while (0)
 
 constexpr int kParamRing = 32;
+constexpr size_t kMaxGraphs = 64;
 constexpr size_t kDefaultWorkspace = size_t(8) << 30;
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -175,14 +176,16 @@ struct mica_ctx {
   bool timing = false;
   std::vector<hipEvent_t> ev_pool;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pending;
-  // launch graphs, one per launch sequence (kernel, block size and LDS of
-  // every launch, and whether timing events are recorded); grid sizes and the
-  // parameter block are set on the instantiated graph before each launch
+  // launch graphs, one per launch sequence (the kernels, and whether timing
+  // events are recorded); grid, block, LDS and the parameter block are set on
+  // the instantiated graph before each launch.  At most kMaxGraphs, the longest
+  // unused goes first.
   struct Graph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<hipGraphNode_t> kernel_nodes;
     hipGraphNode_t ev_begin = nullptr, ev_end = nullptr;
+    int64_t used = 0;  // its last launch
   };
   std::map<std::vector<uint64_t>, Graph> graphs;
   int64_t graph_launches = 0, graph_builds = 0;

@@ -201,15 +201,22 @@ mica_status_t run_sequence(mica_ctx* c, const std::vector<Launch>& seq, const Pa
     }
     return MICA_OK;
   }
+  // (grid, block and LDS are set on the graph: the LDS of the seeded kernels
+  // follows the batch's length bounds)
   std::vector<uint64_t> key;
   key.push_back(timing ? 1 : 0);
-  for (const Launch& l : seq) {
-    key.push_back((uint64_t)(uintptr_t)l.fn);
-    key.push_back(((uint64_t)l.block << 32) | (uint64_t)l.shmem);
-    key.push_back(l.fill ? 1 : 0);
-  }
+  for (const Launch& l : seq) key.push_back((uint64_t)(uintptr_t)l.fn << 1 | (l.fill ? 1 : 0));
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
+    if (c->graphs.size() >= kMaxGraphs) {
+      auto old = c->graphs.begin();
+      for (auto g = c->graphs.begin(); g != c->graphs.end(); ++g)
+        if (g->second.used < old->second.used) old = g;
+      HIP_TRY(hipDeviceSynchronize());  // it may still run
+      (void)hipGraphExecDestroy(old->second.exec);
+      (void)hipGraphDestroy(old->second.graph);
+      c->graphs.erase(old);
+    }
     mica_ctx::Graph g;
     mica_status_t st = build_graph(c, seq, timing, dp, t0, t1, &g);
     if (st != MICA_OK) return st;
@@ -226,8 +233,8 @@ mica_status_t run_sequence(mica_ctx* c, const std::vector<Launch>& seq, const Pa
       HIP_TRY(hipGraphExecEventRecordNodeSetEvent(g.exec, g.ev_end, t1));
     }
   }
+  it->second.used = ++c->graph_launches;
   HIP_TRY(hipGraphLaunch(it->second.exec, stream));
-  c->graph_launches++;
   return MICA_OK;
 }
 
@@ -341,8 +348,7 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   S.pr_rec_bytes = traced ? (uint64_t)(m / 2 + 1) * 256 : 0;
   S.pr_slot_bytes = std::max<uint64_t>(
       align_up(S.pr_rec_bytes + (traced ? (size_t)8 * (size_t)(m + n + 2) * 4 : 0), 256), 256);
-  // blocks of four waves, or fewer where their LDS would pass 62 KB (rounded,
-  // so that batches of similar bounds share their launch graph)
+  // blocks of four waves, or fewer where their LDS would pass 62 KB
   auto block = [](int words, int* threads, size_t* shmem) {
     const size_t bytes = (size_t)words * 4;
     *threads = bytes * 4 <= (size_t)63488 ? 256 : (bytes * 2 <= (size_t)63488 ? 128 : 64);
@@ -852,6 +858,12 @@ mica_status_t mica_dp_align_batch(mica_ctx_t c, const mica_batch_t* b, const mic
   c->last_slots = (int)slots;
   c->last_scratch = scratch_bytes;
   return MICA_OK;
+}
+
+// (for the tests: launch graphs built so far, and held)
+void mica_ctx_graphs(mica_ctx_t c, int64_t* built, int64_t* held) {
+  *built = c->graph_builds;
+  *held = (int64_t)c->graphs.size();
 }
 
 mica_status_t mica_ctx_set_timing(mica_ctx_t c, int enable) {
