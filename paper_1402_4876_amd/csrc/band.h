@@ -316,8 +316,7 @@ __device__ __forceinline__ void band_refill(const Params* __restrict__ prm, cons
   T Hd[NS], Ic[NS], msk[NS];
   uint32_t acc[NS];
   const uint16_t* gwl = gw + l;
-  const uint32_t inner = l == 0 ? 0u : ~0u;  // no deletion comes in from another group
-  (void)inner;
+  [[maybe_unused]] const uint32_t inner = l == 0 ? 0u : ~0u;  // no deletion comes in from another group
   // the score table's low half as a register operand of the lookup
   uint32_t tab_lo_v;
   asm("v_mov_b32 %0, %1" : "=v"(tab_lo_v) : "s"(tab_lo));

@@ -359,7 +359,9 @@ mica_status_t plan_prune(int device, const uint8_t* class_of_m, const mica_batch
   const int wide = (flags & MICA_FORCE_INT32) ? 1 : 0;
   fp->scan_fn = kernels().seed_scan[traced][wide];
   fp->sample_fn = kernels().seed_sample[traced][wide];
-  fp->sampled = b->n_pairs >= kSamplePairs && (!traced || m < kSampleRead);
+  // (an extension needs no part, so its band is nearly always known)
+  fp->sampled = b->n_pairs >= kSamplePairs && (!traced || m < kSampleRead) &&
+                (any_mode[MICA_MODE_SEMIGLOBAL] || any_mode[MICA_MODE_LOCAL]);
   int n_prune = 0;
   for (int md = 0; md < kNumModes; ++md) {
     if (!any_mode[md]) continue;

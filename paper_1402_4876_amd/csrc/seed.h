@@ -82,7 +82,7 @@ constexpr int kBandEntry = 3;
 static_assert((kBandItem + 2 * kBandAgain) * kBandEntry <= kBandStaticWords, "the host sizes the LDS by this");
 
 // A listed pair's band: lowest diagonal, diagonals on both sides of the core
-// (kProven: nothing to check afterwards), strips.
+// (kProven: nothing to check afterwards), width in 16 diagonals.
 constexpr int kProven = 255;
 __device__ __forceinline__ uint32_t band_word(int lo, int margin, int ns) {
   return ((uint32_t)(lo + 32768) & 0xFFFFu) | ((uint32_t)margin << 16) | ((uint32_t)ns << 24);
@@ -581,9 +581,10 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, bool v
       lo = c0 - margin;
     }
   }
-  // (a band's cell costs some four of the table's, whose traced pairs refill 16
-  // diagonals besides: wide bands of short extensions cost more than their tables)
-  if (EXT && busy && (ns > 2 ? 512 : 256) > 3 * (n + (TRACE ? 64 : 0))) ns = 99;
+  // (a band's cell costs some four of the table's: wide bands of short extensions
+  // more than their scores; not more than a traceback, where a few pairs left
+  // take the time of a whole round of items)
+  if (EXT && !TRACE && busy && (ns > 2 ? 512 : 256) > 3 * n) ns = 99;
   const bool go = ok && !direct && ns <= 4;
   if constexpr (!SAMPLE) {
     if (go && x == 0) {
@@ -785,11 +786,10 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, int t
   constexpr bool EXT = (MODE == 2);
   constexpr bool TRACK = (MODE != 0);
   const int lane = threadIdx.x & 63;
-  constexpr int NS = 1;
   const int bg = lane / LG;
   const int l = lane & (LG - 1);
   MICA_GLOBAL uint32_t* rec = (MICA_GLOBAL uint32_t*)slot;
-  BandFind<T, NS> find;
+  BandFind<T, 1> find;
   {
     const MICA_GLOBAL uint32_t* __restrict__ ref2b = G(prm->ref2b);
     const MICA_GLOBAL uint32_t* __restrict__ reads2b = G(prm->reads2b);
@@ -892,20 +892,17 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, int t
       else return (T)v0;
     };
     find.m = pack(mm[0], mm[NP - 1]);
+    find.best[0] = LOCAL ? pack(-d0[0], -d0[NP - 1]) : (T)V::kNeg;
+    find.row[0] = (T)0;
+    find.end[0] = (T)V::kNeg;
+    int lim[2];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      find.best[s] = LOCAL ? pack(-d0[0], -d0[NP - 1]) : (T)V::kNeg;
-      find.row[s] = (T)0;
-      find.end[s] = (T)V::kNeg;
-      int lim[2];
-#pragma unroll
-      for (int h = 0; h < NP; ++h) {
-        const int e = nn[h] - (dlo[h] + 16 * s + l);
-        lim[h] = EXT && mm[h] < e ? mm[h] : e;
-      }
-      find.lim[s] = pack(lim[0], lim[NP - 1]);
+    for (int h = 0; h < NP; ++h) {
+      const int e = nn[h] - (dlo[h] + l);
+      lim[h] = EXT && mm[h] < e ? mm[h] : e;
     }
-    band_refill<V, MODE, NS, TRACE, true, LG>(prm, dlo, W, d0, h0, act, rows_u, 1, mr_u, tail_u, gq, gw, rec, &find);
+    find.lim[0] = pack(lim[0], lim[NP - 1]);
+    band_refill<V, MODE, 1, TRACE, true, LG>(prm, dlo, W, d0, h0, act, rows_u, 1, mr_u, tail_u, gq, gw, rec, &find);
   }
   if constexpr (TRACE) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   lds_wait();
@@ -941,27 +938,22 @@ __device__ __forceinline__ void prune_band(const Params* __restrict__ prm, int t
     constexpr int kNone = -(1 << 28);  // below every score; its loss is certain of nothing
     int b0 = kNone, key0 = 0x7FFFFFFF;  // row m
     int b1 = kNone, key1 = 0x7FFFFFFF;  // any row
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const int gl = 16 * s + l;
-      const int dl = dlo + gl;
-      if (act && gl < W) {
-        if (!LOCAL) {
-          const int j = m + dl;
-          const int v = V::get(find.end[s], h) + top;
-          if (j >= 0 && j <= n && v > b0) {  // (j grows with s)
-            b0 = v;
-            key0 = j;
-          }
+    const int dl = dlo + l;
+    if (act && l < W) {
+      if (!LOCAL) {
+        const int j = m + dl;
+        const int v = V::get(find.end[0], h) + top;
+        if (j >= 0 && j <= n && v > b0) {
+          b0 = v;
+          key0 = j;
         }
-        if (TRACK) {
-          const int v = V::get(find.best[s], h) + top;
-          const int i = V::get(find.row[s], h) - top;
-          const int key = ((i + dl) << 11) | i;
-          if (i >= 1 && (v > b1 || (v == b1 && key < key1))) {
-            b1 = v;
-            key1 = key;
-          }
+      }
+      if (TRACK) {
+        const int v = V::get(find.best[0], h) + top;
+        const int i = V::get(find.row[0], h) - top;
+        if (i >= 1 && v > b1) {
+          b1 = v;
+          key1 = ((i + dl) << 11) | i;
         }
       }
     }

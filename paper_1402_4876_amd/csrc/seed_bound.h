@@ -178,8 +178,8 @@ __host__ __device__ __forceinline__ int leave_saves2(int lose2, int leave2, int 
   return lose2 * k - (parts > 0 ? parts * leave2 : 0);
 }
 
-// Strips of 16 diagonals that hold the core and w diagonals on both sides, and
-// the diagonals ns strips leave on each.
+// How many times 16 diagonals hold the core and w diagonals on both sides, and
+// the diagonals that ns times 16 leave on each.
 __host__ __device__ __forceinline__ int band_strips(int span, int w) { return (span + 1 + 2 * w + 15) >> 4; }
 __host__ __device__ __forceinline__ int band_margin(int span, int ns) { return (16 * ns - (span + 1)) >> 1; }
 
