@@ -44,11 +44,11 @@
 // too narrow is aligned again in a wider one by the same wave.  k_seed_left:
 // the full traceback of the pairs left, where there are few.
 //
-// What bounds them: VALU instructions (scan 390, bands 630 per pair of 10^6
+// What bounds them: VALU instructions (scan 390, bands 603 per pair of 10^6
 // reads of 150 in windows of 400, of which 57% are answered by the scan and
 // 0.1% left; the full table takes 6,460) and, in small batches, the latency
 // of one band (60 us for 48 pairs of 76 to 151 bases).  10^6 x 150 x 400: scan
-// 0.70 ms, bands 1.32 ms, left pairs 0.12 ms, in place of 10.7 ms of fills and
+// 0.70 ms, bands 1.35 ms, left pairs 0.12 ms, in place of 10.7 ms of fills and
 // 1.3 ms of side lists.
 #pragma once
 
