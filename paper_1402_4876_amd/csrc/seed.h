@@ -248,10 +248,22 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, bool v
     uint32_t* const pq = part + q * TN;
     for (int s = x; s < tmax; s += 8) pq[s] = s < T ? (lds_bases(rd + q * RN, kSeed * s) << 8) | (uint32_t)s : 0xFFFFFF00u | (uint32_t)s;
     lds_wait();
+    // each part against every other (pads of equal bases count too: such a
+    // pair is only left to the fills)
+    for (int s = x; s < tmax; s += 8) {
+      const uint32_t k = pq[s];
+      int same = 0;
+      for (int s2 = 0; s2 < tmax; s2 += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) same += (k ^ pq[s2 + u]) < 256u ? 1 : 0;
+      twin |= s < T && same > 1;
+    }
+    twin = (__ballot(twin) >> (8 * q) & 0xFFu) != 0;
     // positions p0 .. p0 + kSeed - 1 of the pair's window, a "tile" per lane;
     // first for four parts: where none of the item's pairs has one of them,
     // the others are not looked for
-    const int tiles = valid && T > 0 ? n / kSeed : 0;  // of the n - kSeed + 1 positions
+    // (reads of tandem repeats would have occurrences everywhere)
+    const int tiles = valid && T > 0 && !twin ? n / kSeed : 0;  // of the n - kSeed + 1 positions
     const int rounds = (wave_max_int(tiles) + 7) >> 3;
     bool any = false;
     for (int from = 0, to = 4; from < tmax; from = to, to = tmax) {
@@ -304,19 +316,8 @@ __device__ __forceinline__ int prune_scan(const Params* __restrict__ prm, bool v
         return 0;
       }
     }
-    // each part against every other (pads of equal bases count too: such a
-    // pair is only left to the fills)
-    for (int s = x; s < tmax; s += 8) {
-      const uint32_t k = pq[s];
-      int same = 0;
-      for (int s2 = 0; s2 < tmax; s2 += 4)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) same += (k ^ pq[s2 + u]) < 256u ? 1 : 0;
-      twin |= s < T && same > 1;
-    }
     lds_wait();
   }
-  twin = (__ballot(twin) >> (8 * q) & 0xFFu) != 0;
 
   // ---- what the scan says of each pair (the same in its 8 lanes) -------------
   bool ok = valid && !twin && band_fits<V>(prm, m, n, h0) && (EXT || T > 0);
